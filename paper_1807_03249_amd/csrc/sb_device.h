@@ -56,6 +56,12 @@ __device__ inline int32_t seed_key(uint32_t q4, short2_t p4, int32_t k) {
   return __builtin_amdgcn_sdot2(dv, dv, k, true);
 }
 
+// Orders a wave's LDS accesses before and after it.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Tile of workgroup `bid` out of n: workgroups are dealt to the 8 XCDs in
 // turn (bid mod 8), so XCD x takes the x-th contiguous run of tiles -- a band
 // of rows -- and its L2 sees the source regions of one band instead of

@@ -3,31 +3,31 @@
 // additional guiding channels of Sec. 3.1, for which the paper suggests a
 // search tree.
 //
-//   tree build   a k-d tree of the source guide, one level per round of
-//                launches.  k_tree_level takes one node per workgroup (its
-//                texels are a contiguous run), computes the node's tight box
-//                and either makes it a leaf (at most kLeafMax texels, the
-//                depth limit, or texels equal in every channel -- then the
-//                one of smallest raster index stands for all) or splits the
-//                widest element (by weight, then by raw range) at the middle
-//                of the box, both sides non-empty, partitioning in one pass
-//                into the other texel buffer (left texels from the front,
-//                right ones from the back).  k_tree_alloc numbers the next
-//                level's nodes in order with a block scan, so the tree is the
-//                same on every run.
-//   search       depth first, nearer child first; a subtree is skipped only
-//                if its box lies strictly farther than the best texel so far
-//                (one at equal distance may hold a smaller raster index), so
-//                the result is the exact argmin of sum_k w_k (q_k - g_k)^2,
-//                ties to the smallest raster index, for any tree shape.
-//   k_seeds_n    eight lanes per padded seed record: the seed and its search,
-//                the lanes searching disjoint subtrees under a shared bound.
+//   tree build   a balanced k-d tree of the source guide, kept as a complete
+//                8-ary tree in level order (see tree_layout): every split is
+//                at the median of the widest element (by weight, then by raw
+//                range) and hands its left child exactly half of the padded
+//                size, so nodes need no links.  Splits of more than
+//                kSortBlock texels run over the chip (k_tree_hist,
+//                k_tree_split); below that one workgroup sorts its
+//                kSortBlock texels in LDS down to runs of eight
+//                (k_tree_sort) and k_tree_top joins the runs' boxes.
+//   search       groups of G lanes per query, one node per step: the lanes
+//                load the node's eight child records (box and smallest
+//                coordinate) in one round trip, descend to the nearest and
+//                leave the others in LDS; the last level's children are the
+//                texels themselves.  A child is skipped only if its box lies
+//                strictly farther than the best texel so far (or equally far
+//                with no smaller raster index in it), so the result is the
+//                exact argmin of sum_k w_k (q_k - g_k)^2, ties to the
+//                smallest raster index, for any tree shape.
+//   k_seeds_n    eight lanes per padded seed record: the seed and its search.
 //   k_assign_n   the level loop of Algorithm 2 per pixel (64 x 16 tiles, four
 //                rows per thread) with the many-channel error; a pixel no
 //                level accepts keeps the nearest candidate its level loop
 //                measured.
-//   k_fallback_n those pixels' own lookups, one thread per pixel, each search
-//                starting from that candidate.
+//   k_fallback_n those pixels' own lookups, listed per 16 x 16 tile, each
+//                search starting from that candidate.
 //   k_tree_query the search of caller-given texels (sb_tree_query).
 #include <stdio.h>
 #include <string.h>
@@ -40,12 +40,14 @@
 namespace sb {
 namespace {
 
-constexpr uint32_t kLeafMax = 8;
-constexpr int32_t kMaxDepth = 32;
+// Texels one workgroup sorts in LDS.
+constexpr uint32_t kSortLog = 11, kSortBlock = 1u << kSortLog;
+// Bins of a split's histogram.
+constexpr uint32_t kBinsLog = 10, kBins = 1u << kBinsLog;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-// Dword-aligned vectors (node records are 8-byte aligned; global loads need
-// dword alignment only).
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+// Dword-aligned vectors (global loads need dword alignment only).
 typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -135,207 +137,126 @@ __device__ __forceinline__ typename DistOf<D>::type tx_dist(const Tx<S> &a, cons
   return d;
 }
 
-// The same sum from q to the nearest point of the box [lo, hi].
+// A texel's elements as 16-bit pairs, so one packed instruction handles two:
+// 8-bit texels as the even and the odd bytes of each word.
 template <int D, int S>
-__device__ __forceinline__ typename DistOf<D>::type box_dist(const Tx<S> &q, const Tx<S> &lo,
+constexpr int kPairs = kElems<D, S> / 2;
+template <int D, int S>
+struct Pairs {
+  u16x2 p[kPairs<D, S>];
+};
+template <int D, int S>
+__device__ __forceinline__ Pairs<D, S> to_pairs(const Tx<S> &t) {
+  Pairs<D, S> r;
+#pragma unroll
+  for (int k = 0; k < S / 4; ++k) {
+    if constexpr (D == 8) {
+      r.p[2 * k] = __builtin_bit_cast(u16x2, t.w[k] & 0x00FF00FFu);
+      r.p[2 * k + 1] = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(0u, t.w[k], 0x0C030C01u));
+    } else {
+      r.p[k] = __builtin_bit_cast(u16x2, t.w[k]);
+    }
+  }
+  return r;
+}
+template <int D, int S>
+__device__ __forceinline__ Tx<S> from_pairs(const Pairs<D, S> &r) {
+  Tx<S> t;
+#pragma unroll
+  for (int k = 0; k < S / 4; ++k) {
+    if constexpr (D == 8)
+      t.w[k] = __builtin_bit_cast(uint32_t, r.p[2 * k]) |
+               (__builtin_bit_cast(uint32_t, r.p[2 * k + 1]) << 8);
+    else t.w[k] = __builtin_bit_cast(uint32_t, r.p[k]);
+  }
+  return t;
+}
+
+// What a search keeps of the style's weights: pairs like a texel's for 8-bit
+// guides (the weights are bytes laid out like one), the words for 16-bit ones.
+template <int D, int S>
+struct Weights {
+  uint32_t w[2];
+  Pairs<8, 8> p;
+  __device__ explicit Weights(const uint32_t *wn) {
+    w[0] = wn[0], w[1] = wn[1];
+    p = to_pairs<8, 8>(Tx<8>{{wn[0], wn[1]}});
+  }
+};
+
+// sum_k w_k d_k^2 from q to the nearest point of the box [lo, hi] (its texel
+// where lo = hi): the two saturating differences of an element are not both
+// above zero, so their union is its distance to the box.
+template <int D, int S>
+__device__ __forceinline__ typename DistOf<D>::type box_dist(const Pairs<D, S> &q, const Tx<S> &lo,
                                                             const Tx<S> &hi,
-                                                            const uint32_t *wn) {
-  typename DistOf<D>::type d = 0;
-  for_elems<0, kElems<D, S>>([&](auto k) {
+                                                            const Weights<D, S> &wt) {
+  const Pairs<D, S> l = to_pairs<D, S>(lo), h = to_pairs<D, S>(hi);
+  typename DistOf<D>::type acc = 0;
+  for_elems<0, kPairs<D, S>>([&](auto k) {
     constexpr int K = decltype(k)::value;
-    const uint32_t v = elem<D, S, K>(q), l = elem<D, S, K>(lo), h = elem<D, S, K>(hi);
-    const uint32_t e = v < l ? l - v : (v > h ? v - h : 0u);
-    const uint32_t e2 = __umul24(e, e);
-    if constexpr (D == 8) d += __umul24(e2, weight<K>(wn));
-    else d += uint64_t(e2) * weight<K>(wn);
+    const u16x2 d = __builtin_elementwise_sub_sat(l.p[K], q.p[K]) |
+                    __builtin_elementwise_sub_sat(q.p[K], h.p[K]);
+    if constexpr (D == 8) {
+      // d <= 255 and w <= 127: their product fits 16 bits
+      acc = __builtin_amdgcn_udot2(d, d * wt.p.p[K], acc, false);
+    } else {
+      const uint32_t d0 = d.x, d1 = d.y;
+      acc += uint64_t(__umul24(d0, weight<2 * K>(wt.w))) * d0;
+      acc += uint64_t(__umul24(d1, weight<2 * K + 1>(wt.w))) * d1;
+    }
   });
-  return d;
+  return acc;
+}
+
+// A distance in 29 bits, weakly monotone (so an order of packed values never
+// contradicts the distances'): 8-bit ones are < 2^26, 16-bit ones < 2^42 as
+// floats without their two lowest fraction bits.
+__device__ __forceinline__ uint32_t pack_dist(uint32_t d) { return d; }
+__device__ __forceinline__ uint32_t pack_dist(uint64_t d) {
+  const float f = __builtin_fmaf(float(uint32_t(d >> 32)), 4294967296.0f, float(uint32_t(d)));
+  return __builtin_bit_cast(uint32_t, f) >> 2;
 }
 
 struct TreeView {
-  const void *nodes;
-  const void *vals;
+  const void *recs;
   const uint32_t *keys;
+  int32_t levels;
 };
 
 TreeView tree_view(const void *tree, size_t n, size_t t) {
   const TreeLayout l = tree_layout(n, t);
   const char *b = static_cast<const char *>(tree);
-  return TreeView{b + l.nodes, b + l.vals, reinterpret_cast<const uint32_t *>(b + l.keys)};
+  return TreeView{b + l.recs, reinterpret_cast<const uint32_t *>(b + l.keys), l.levels};
 }
 
-// A node record: box [lo, hi] and link (see tree_layout).
-template <int S>
-struct Rec {
-  Tx<S> lo, hi;
-  u32x2 link;
-};
-
-template <int S>
-__device__ __forceinline__ const SB_GLOBAL unsigned char *rec_at(const void *nodes, uint32_t i) {
-  return glb(static_cast<const unsigned char *>(nodes)) + uint64_t(i) * tree_record_bytes(S);
-}
-
-template <int S>
-__device__ __forceinline__ Rec<S> load_rec(const void *nodes, uint32_t i) {
-  const SB_GLOBAL unsigned char *p = rec_at<S>(nodes, i);
-  Rec<S> r;
-  if constexpr (S == 4) {
-    const u32x4a4 v = *reinterpret_cast<const SB_GLOBAL u32x4a4 *>(p);
-    r.lo.w[0] = v.x, r.hi.w[0] = v.y, r.link = u32x2{v.z, v.w};
-  } else if constexpr (S == 8) {
-    const u32x4a4 v = *reinterpret_cast<const SB_GLOBAL u32x4a4 *>(p);
-    const u32x2a4 m = *reinterpret_cast<const SB_GLOBAL u32x2a4 *>(p + 16);
-    r.lo.w[0] = v.x, r.lo.w[1] = v.y, r.hi.w[0] = v.z, r.hi.w[1] = v.w, r.link = u32x2{m.x, m.y};
-  } else {
-    const u32x4a4 a = *reinterpret_cast<const SB_GLOBAL u32x4a4 *>(p);
-    const u32x4a4 b = *reinterpret_cast<const SB_GLOBAL u32x4a4 *>(p + 16);
-    const u32x2a4 m = *reinterpret_cast<const SB_GLOBAL u32x2a4 *>(p + 32);
-    r.lo.w[0] = a.x, r.lo.w[1] = a.y, r.lo.w[2] = a.z, r.lo.w[3] = a.w;
-    r.hi.w[0] = b.x, r.hi.w[1] = b.y, r.hi.w[2] = b.z, r.hi.w[3] = b.w;
-    r.link = u32x2{m.x, m.y};
-  }
-  return r;
+// The records of entries i .. i + N - 1.
+template <int S, int N>
+__device__ __forceinline__ void load_recs(const void *recs, uint32_t i, Tx<S> *lo, Tx<S> *hi) {
+  constexpr int W = 2 * S / 4 * N, V = W % 4 == 0 ? 4 : 2;  // words, words per load
+  typedef uint32_t vec __attribute__((ext_vector_type(V), aligned(4)));
+  const SB_GLOBAL vec *p = reinterpret_cast<const SB_GLOBAL vec *>(
+      glb(static_cast<const unsigned char *>(recs)) + uint64_t(i * uint32_t(2 * S)));
+  vec v[W / V];
+#pragma unroll
+  for (int k = 0; k < W / V; ++k) v[k] = p[k];
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int k = 0; k < S / 4; ++k) {
+      const int l = n * (S / 2) + k, h = l + S / 4;
+      lo[n].w[k] = v[l / V][l % V];
+      hi[n].w[k] = v[h / V][h % V];
+    }
 }
 
 template <int S>
-__device__ __forceinline__ void store_rec_box(void *nodes, uint32_t i, const Tx<S> &lo,
-                                              const Tx<S> &hi) {
+__device__ __forceinline__ void store_rec(void *recs, uint32_t i, const Tx<S> &lo,
+                                          const Tx<S> &hi) {
   SB_GLOBAL uint32_t *p = reinterpret_cast<SB_GLOBAL uint32_t *>(
-      const_cast<SB_GLOBAL unsigned char *>(rec_at<S>(nodes, i)));
+      glb(static_cast<unsigned char *>(recs)) + uint64_t(i * uint32_t(2 * S)));
 #pragma unroll
   for (int k = 0; k < S / 4; ++k) p[k] = lo.w[k], p[S / 4 + k] = hi.w[k];
-}
-
-__device__ __forceinline__ void store_rec_link(void *nodes, uint32_t rec_bytes, uint32_t i,
-                                               u32x2 link) {
-  SB_GLOBAL uint32_t *p = reinterpret_cast<SB_GLOBAL uint32_t *>(
-      glb(static_cast<unsigned char *>(nodes)) + uint64_t(i) * rec_bytes + (rec_bytes - 8));
-  p[0] = link.x;
-  p[1] = link.y;
-}
-
-// Texels i .. i + kLeafGroup - 1 of the tree's leaves and their keys.
-template <int S>
-__device__ __forceinline__ void load_group(const TreeView &tv, uint32_t i, Tx<S> *t,
-                                           uint32_t *k) {
-  static_assert(kLeafGroup == 4, "groups of four texels");
-  const SB_GLOBAL u32x4a4 *v = reinterpret_cast<const SB_GLOBAL u32x4a4 *>(
-      glb(static_cast<const unsigned char *>(tv.vals)) + uint64_t(i) * S);
-  constexpr int W = S / 4;  // words per texel
-  u32x4 w[W];
-#pragma unroll
-  for (int n = 0; n < W; ++n) w[n] = v[n];
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int c = 0; c < W; ++c) t[m].w[c] = w[(m * W + c) / 4][(m * W + c) % 4];
-  const u32x4 kk = *reinterpret_cast<const SB_GLOBAL u32x4a4 *>(glb(tv.keys) + i);
-  k[0] = kk.x, k[1] = kk.y, k[2] = kk.z, k[3] = kk.w;
-}
-
-// A deferred sibling on the search stack: its link and box distance.  For
-// 8-bit guides one 8-byte entry, the link packed into a word (inner: the
-// first child, < 2^27; leaf: kTreeLeaf | count << 27 | first texel, count
-// <= kLeafMax, first texel < 2^26), for 16-bit ones 16 bytes.
-template <int D>
-struct StackOf {
-  typedef u32x4 type;
-};
-template <>
-struct StackOf<8> {
-  typedef u32x2 type;
-};
-template <int D>
-__device__ __forceinline__ typename StackOf<D>::type push_entry(u32x2 l,
-                                                                typename DistOf<D>::type b) {
-  if constexpr (D == 8) {
-    const uint32_t w = (l.y & kTreeLeaf) ? (kTreeLeaf | ((l.y & ~kTreeLeaf) << 27) | l.x) : l.x;
-    return u32x2{w, b};
-  } else {
-    return u32x4{l.x, l.y, uint32_t(b), uint32_t(uint64_t(b) >> 32)};
-  }
-}
-template <int D>
-__device__ __forceinline__ void pop_entry(const typename StackOf<D>::type &e, u32x2 &l,
-                                          typename DistOf<D>::type &b) {
-  if constexpr (D == 8) {
-    l = u32x2{e.x & 0x07FFFFFFu, (e.x & kTreeLeaf) ? (kTreeLeaf | ((e.x >> 27) & 15u)) : 0u};
-    b = e.y;
-  } else {
-    l = u32x2{e.x, e.y};
-    b = typename DistOf<D>::type(e.z) | (typename DistOf<D>::type(e.w) << 32);
-  }
-}
-
-// The exact lookup of q: the source coordinate x | y << 16 of the texel
-// nearest to q under the weights, ties to the smallest raster index (the
-// coordinate word y << 16 | x orders like the raster index).  An inner node
-// loads both children's records at once (boxes and links), so each level of
-// the descent costs one round trip; a deferred sibling is kept with its link
-// and its box distance.  The stack holds at most one deferred sibling per
-// tree level of the current path, and inner nodes lie above depth
-// kMaxDepth - 1.
-//
-// (best, best_key) may start at a real source texel's distance and
-// coordinate (a candidate the caller already measured): every subtree that
-// could hold a texel at that distance or nearer is still visited, so the
-// result is the same, found with fewer visits.
-template <int D, int S>
-__device__ uint32_t tree_search(const TreeView &tv, const Tx<S> &q, const uint32_t *wn,
-                                typename DistOf<D>::type best = ~typename DistOf<D>::type(0),
-                                uint32_t best_key = 0xFFFFFFFFu) {
-  typedef typename DistOf<D>::type Dist;
-  // one entry per deferred sibling (its link and bound): one scratch store
-  // per push and one load per pop, the load issued with a leaf's texels
-  // when a leaf comes before the pop
-  typename StackOf<D>::type stack[kMaxDepth];
-  int32_t sp = 0;
-  u32x2 link = load_rec<S>(tv.nodes, 0).link;
-  Dist bound = 0;
-  for (;;) {
-    typename StackOf<D>::type nxt = {};
-    if (bound <= best) {
-      if (link.y & kTreeLeaf) {
-        // the entry popped after this leaf, loaded with the leaf's texels
-        if (sp > 0) nxt = stack[sp - 1];
-        // the leaf's texels and keys in groups of kLeafGroup, each group's
-        // loads issued together (the tree has room past its last entries)
-        const uint32_t cnt = link.y & ~kTreeLeaf;
-        for (uint32_t j = 0; j < cnt; j += kLeafGroup) {
-          Tx<S> t[kLeafGroup];
-          uint32_t k[kLeafGroup];
-          load_group<S>(tv, link.x + j, t, k);
-#pragma unroll
-          for (uint32_t m = 0; m < kLeafGroup; ++m) {
-            const Dist d = tx_dist<D, S>(q, t[m], wn);
-            if (j + m < cnt && (d < best || (d == best && k[m] < best_key)))
-              best = d, best_key = k[m];
-          }
-        }
-      } else {
-        const Rec<S> r0 = load_rec<S>(tv.nodes, link.x);
-        const Rec<S> r1 = load_rec<S>(tv.nodes, link.x + 1);
-        const Dist b0 = box_dist<D, S>(q, r0.lo, r0.hi, wn);
-        const Dist b1 = box_dist<D, S>(q, r1.lo, r1.hi, wn);
-        const bool first0 = b0 <= b1;
-        const Dist bf = first0 ? b1 : b0;
-        if (bf <= best) {
-          const u32x2 fl = first0 ? r1.link : r0.link;
-          stack[sp++] = push_entry<D>(fl, bf);
-        }
-        link = first0 ? r0.link : r1.link;
-        bound = first0 ? b0 : b1;
-        continue;
-      }
-    }
-    if (sp == 0) break;
-    const typename StackOf<D>::type e =
-        (link.y & kTreeLeaf) && bound <= best ? nxt : stack[sp - 1];
-    --sp;
-    pop_entry<D>(e, link, bound);
-  }
-  return best_key;
 }
 
 // v of another lane of the row by the DPP pattern CTRL (every lane of the
@@ -350,301 +271,606 @@ __device__ __forceinline__ uint64_t dpp_from(uint64_t v) {
   return lo | (hi << 32);
 }
 
-// The least of v over each aligned group of 8 lanes, in every lane of the
-// group (all eight active): pairs within quads (lane ^ 1, lane ^ 2), then
-// the group's two quads (lane 7 - i of the group).
-template <class T>
-__device__ __forceinline__ T group8_min(T v) {
+// The least of v over each aligned group of G lanes, in every lane of the
+// group (all active): lane ^ 1, lane ^ 2, then the group's two quads (lane
+// 7 - i of the group).
+template <int G, class T>
+__device__ __forceinline__ T group_min(T v) {
+  static_assert(G == 2 || G == 4 || G == 8, "groups of 2, 4 or 8 lanes");
   v = min(v, dpp_from<0xB1>(v));
-  v = min(v, dpp_from<0x4E>(v));
-  return min(v, dpp_from<0x141>(v));
+  if constexpr (G >= 4) v = min(v, dpp_from<0x4E>(v));
+  if constexpr (G >= 8) v = min(v, dpp_from<0x141>(v));
+  return v;
 }
 
-// The same lookup by an aligned group of 8 lanes given the same q: lane g
-// of the group searches the subtree reached from the root by the path of
-// g's three bits (a leaf met on the way is searched by the one lane whose
-// remaining bits are zero), one node per step, and every step prunes with
-// the group's best distance so far, which every lane's subtree search may
-// use: a subtree farther than a texel any lane has found holds no texel at
-// the least distance.  The group's nearest texel, ties to the smallest key,
-// is returned to every lane; the subtrees partition the texels, so the
-// result is the search's own.
-template <int D, int S>
-__device__ uint32_t tree_search_group8(const TreeView &tv, const Tx<S> &q, const uint32_t *wn,
-                                       uint32_t g) {
+// The exact lookup of a texel by an aligned group of G lanes, one tree node
+// per step: the source coordinate x | y << 16 of the texel nearest to q under
+// the weights, ties to the smallest raster index.  Lane g takes the node's
+// children g N .. g N + N - 1 (N = 8 / G): their records come in one round
+// trip, the nearest child is next and the lanes keep the others' packed
+// distances in LDS, one slot per level of the path (`live`: the levels whose
+// slot may still hold a child), so nothing is kept in scratch memory and
+// there is one dependent round trip per node.
+//
+// (best, best_key) may start at a real source texel's distance and
+// coordinate (a candidate the caller already measured): every subtree that
+// could hold a texel at that distance or nearer is still visited, so the
+// result is the same, found with fewer steps.
+template <int D, int S, int G>
+struct Search {
   typedef typename DistOf<D>::type Dist;
-  Dist best = ~Dist(0), bound = 0;
-  uint32_t best_key = 0xFFFFFFFFu;
-  u32x2 link = load_rec<S>(tv.nodes, 0).link;
-  bool done = false;
-#pragma unroll
-  for (int l = 0; l < 3; ++l) {
-    if (link.y & kTreeLeaf) {
-      done = (g >> l) != 0u;
-      break;
-    }
-    const Rec<S> r = load_rec<S>(tv.nodes, link.x + ((g >> l) & 1u));
-    link = r.link;
-    bound = box_dist<D, S>(q, r.lo, r.hi, wn);
+  static constexpr int N = 8 / G;
+  static constexpr uint32_t kGone = 0xFFFFFFFFu;  // a slot entry without a child
+  Pairs<D, S> q;
+  Dist best;
+  uint32_t best_key, pos, live;
+  int32_t depth;
+
+  __device__ __forceinline__ void start(const Tx<S> &t, Dist b, uint32_t k) {
+    q = to_pairs<D, S>(t);
+    best = b, best_key = k;
+    pos = live = 0u;
+    depth = 0;
   }
-  typename StackOf<D>::type stack[kMaxDepth];
-  int32_t sp = 0;
-  const uint32_t base = __lane_id() & ~7u;
-  for (;;) {
-    const Dist gb = group8_min(best);
-    if (((__ballot(done) >> base) & 0xFFu) == 0xFFu) break;
-    if (done) continue;
-    if (bound <= gb) {
-      if (link.y & kTreeLeaf) {
-        const uint32_t cnt = link.y & ~kTreeLeaf;
-        for (uint32_t j = 0; j < cnt; j += kLeafGroup) {
-          Tx<S> t[kLeafGroup];
-          uint32_t k[kLeafGroup];
-          load_group<S>(tv, link.x + j, t, k);
+  __device__ __forceinline__ static uint32_t least(const uint32_t *pk) {
+    uint32_t m = pk[0];
 #pragma unroll
-          for (uint32_t m = 0; m < kLeafGroup; ++m) {
-            const Dist d = tx_dist<D, S>(q, t[m], wn);
-            if (j + m < cnt && (d < best || (d == best && k[m] < best_key)))
-              best = d, best_key = k[m];
-          }
-        }
-      } else {
-        const Rec<S> r0 = load_rec<S>(tv.nodes, link.x);
-        const Rec<S> r1 = load_rec<S>(tv.nodes, link.x + 1);
-        const Dist b0 = box_dist<D, S>(q, r0.lo, r0.hi, wn);
-        const Dist b1 = box_dist<D, S>(q, r1.lo, r1.hi, wn);
-        const bool first0 = b0 <= b1;
-        const Dist bf = first0 ? b1 : b0;
-        if (bf <= gb) stack[sp++] = push_entry<D>(first0 ? r1.link : r0.link, bf);
-        link = first0 ? r0.link : r1.link;
-        bound = first0 ? b0 : b1;
-        continue;
+    for (int j = 1; j < N; ++j) m = min(m, pk[j]);
+    return group_min<G>(m);
+  }
+  // Take the nearest child m of level d's slot values pk; the rest stay.
+  __device__ __forceinline__ void descend(uint32_t m, int32_t d, uint32_t *pk, uint32_t *slots) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) pk[j] = pk[j] == m ? kGone : pk[j];
+    if (least(pk) != kGone) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) slots[64 * N * d + j] = pk[j];
+      live |= 1u << d;
+    } else {
+      live &= ~(1u << d);
+    }
+    pos = 8u * (pos >> (3 * (depth - d))) + (m & 7u);
+    depth = d + 1;
+  }
+  // One node; true when the search is over.  `slots`: the lane's N words of
+  // level 0, a level every 64 N words.
+  __device__ __forceinline__ bool step(const TreeView &tv, const Weights<D, S> &wt,
+                                       uint32_t *slots) {
+    const uint32_t c0 = N * (threadIdx.x & uint32_t(G - 1));
+    const uint32_t i = tree_start(depth + 1) + 8u * pos + c0;
+    Tx<S> lo[N], hi[N];
+    uint32_t key[N];
+    load_recs<S, N>(tv.recs, i, lo, hi);
+#pragma unroll
+    for (int j = 0; j < N; ++j) key[j] = glb(tv.keys)[i + uint32_t(j)];
+    Dist d[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) d[j] = box_dist<D, S>(q, lo[j], hi[j], wt);
+    uint32_t pk[N];
+    if (depth + 1 == tv.levels) {  // the children are texels
+      Dist dm = ~Dist(0);
+      uint32_t km = kNoTreeKey;
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (key[j] != kNoTreeKey && (d[j] < dm || (d[j] == dm && key[j] < km)))
+          dm = d[j], km = key[j];
+      const Dist gd = group_min<G>(dm);
+      const uint32_t gk = group_min<G>(dm == gd ? km : kNoTreeKey);
+      if (gd < best || (gd == best && gk < best_key)) best = gd, best_key = gk;
+    } else {
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const bool in = key[j] != kNoTreeKey &&
+                        (d[j] < best || (d[j] == best && key[j] < best_key));
+        pk[j] = in ? (pack_dist(d[j]) << 3) | (c0 + uint32_t(j)) : kGone;
+      }
+      const uint32_t m = least(pk);
+      if (m != kGone) {
+        descend(m, depth, pk, slots);
+        return false;
       }
     }
-    if (sp == 0) {
-      done = true;
-      continue;
+    // back to the deepest level with a child left that is not farther than
+    // the best so far
+    const uint32_t reach = (pack_dist(best) << 3) | 7u;
+    while (live != 0u) {
+      const int32_t l = 31 - __builtin_clz(live);
+#pragma unroll
+      for (int j = 0; j < N; ++j) pk[j] = slots[64 * N * l + j];
+      const uint32_t m = least(pk);
+      if (m <= reach) {
+        descend(m, l, pk, slots);
+        return false;
+      }
+      live &= ~(1u << l);
     }
-    --sp;
-    pop_entry<D>(stack[sp], link, bound);
+    return true;
   }
-  // the group's nearest: least distance, then least key
-  const Dist dmin = group8_min(best);
-  return group8_min(best == dmin ? best_key : 0xFFFFFFFFu);
+};
+
+// LDS bytes of a 256-thread workgroup's searches (Search::step's slots: one
+// level of the path per tree level above the texels).
+template <int G>
+unsigned stack_bytes(int32_t levels) {
+  return unsigned(levels - 1) * 256u * (8u / G) * 4u;
+}
+template <int G>
+__device__ __forceinline__ uint32_t *lane_slots(const TreeView &tv, uint32_t *stack) {
+  return stack + (8 / G) * (64u * uint32_t(tv.levels - 1) * (threadIdx.x >> 6) +
+                            (threadIdx.x & 63u));
+}
+
+template <int D, int S, int G>
+__device__ uint32_t tree_search(const TreeView &tv, const Tx<S> &q, const uint32_t *wn,
+                                uint32_t *stack) {
+  typedef typename DistOf<D>::type Dist;
+  const Weights<D, S> wt(wn);
+  uint32_t *slots = lane_slots<G>(tv, stack);
+  Search<D, S, G> s;
+  s.start(q, ~Dist(0), kNoTreeKey);
+  while (!s.step(tv, wt, slots)) {
+  }
+  return s.best_key;
 }
 
 // ---------------------------------------------------------------- tree build
 
-struct BuildArgs {
-  const u32x4 *list_in;  // this level's nodes {first texel, count, node, 0}
-  u32x2 *res;            // per list entry {split, texels left of the split}
-  const void *vals_in;
-  const uint32_t *keys_in;
-  void *vals_out;  // the next level's texels (split nodes' children)
+// Words of a segment's box: every element's lowest value, then the inverse
+// of its highest, so that both are minima.
+template <int D, int S>
+constexpr uint32_t kBoxWords = 2 * kElems<D, S>;
+
+// The texels of the splits so far: from a split's output, or (keys null) the
+// guide in raster order.
+struct TexelsIn {
+  const void *vals;
+  const uint32_t *keys;
+  uint32_t n, sw;
+};
+__device__ __forceinline__ uint32_t texel_key(const TexelsIn &t, uint32_t i) {
+  return t.keys ? glb(t.keys)[i] : ((i / t.sw) << 16) | (i % t.sw);
+}
+
+struct SplitArgs {
+  TexelsIn in;
+  void *vals_out;
   uint32_t *keys_out;
-  void *nodes;     // the tree's sections
-  void *tvals;
-  uint32_t *tkeys;
-  uint32_t wn[2];  // build weights (split choice only)
+  uint32_t *boxes, *hist, *ctr;  // per segment: kBoxWords, kBins, 4 words
+  int32_t level, lg;             // this level's segments hold 2^lg texels
+  int32_t last;                  // the children are k_tree_sort's blocks
+  uint32_t wn[2];                // build weights (split choice only)
   int32_t channels;
 };
 
-template <int S>
-__global__ void __launch_bounds__(256) k_tree_init(const void *guide, uint32_t n, uint32_t sw,
-                                                   void *vals, uint32_t *keys, u32x4 *list) {
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) {
-    store_tx<S>(vals, i, load_tx<S>(guide, i));
-    glb(keys)[i] = ((i / sw) << 16) | (i % sw);
-  }
-  if (i == 0) glb(list)[0] = u32x4{0u, n, 0u, 0u};
-}
-
-// One node per workgroup of NT threads (1024 while the level's nodes are
-// large, else 256).
-template <int D, int S, int NT>
-__global__ void __launch_bounds__(NT) k_tree_level(BuildArgs a, int32_t depth) {
-  constexpr int E = kElems<D, S>;
-  constexpr uint32_t NW = NT / 64;
-  __shared__ uint32_t s_lo[8], s_hi[8], s_key, s_wave[NW];
-  const u32x4 ent = glb(a.list_in)[blockIdx.x];
-  const uint32_t b = ent.x, c = ent.y, node = ent.z, tid = threadIdx.x;
-  if (tid < 8) s_lo[tid] = 0xFFFFFFFFu, s_hi[tid] = 0u;
-  if (tid == 0) s_key = 0xFFFFFFFFu;
-  __syncthreads();
-  // the node's box; four texels per thread in flight
-  uint32_t lo[E], hi[E];
-#pragma unroll
-  for (int k = 0; k < E; ++k) lo[k] = 0xFFFFFFFFu, hi[k] = 0u;
-  auto widen = [&](const Tx<S> &t) {
-    for_elems<0, E>([&](auto k) {
-      constexpr int K = decltype(k)::value;
-      lo[K] = min(lo[K], elem<D, S, K>(t));
-      hi[K] = max(hi[K], elem<D, S, K>(t));
-    });
-  };
-  uint32_t i = b + tid;
-  for (; i + 3 * NT < b + c; i += 4 * NT) {
-    const Tx<S> t0 = load_tx<S>(a.vals_in, i), t1 = load_tx<S>(a.vals_in, i + NT);
-    const Tx<S> t2 = load_tx<S>(a.vals_in, i + 2 * NT), t3 = load_tx<S>(a.vals_in, i + 3 * NT);
-    widen(t0), widen(t1), widen(t2), widen(t3);
-  }
-  for (; i < b + c; i += NT) widen(load_tx<S>(a.vals_in, i));
-  if (tid < c) {
-#pragma unroll
-    for (int k = 0; k < E; ++k) atomicMin(&s_lo[k], lo[k]), atomicMax(&s_hi[k], hi[k]);
-  }
-  __syncthreads();
-  Tx<S> blo, bhi;
-#pragma unroll
-  for (int k = 0; k < S / 4; ++k) blo.w[k] = 0u, bhi.w[k] = 0u;
-#pragma unroll
-  for (int k = 0; k < E; ++k) {
-    const int sh = D == 8 ? (k & 3) * 8 : (k & 1) * 16, wi = D == 8 ? k >> 2 : k >> 1;
-    blo.w[wi] |= s_lo[k] << sh;
-    bhi.w[wi] |= s_hi[k] << sh;
-  }
-  if (tid == 0) store_rec_box<S>(a.nodes, node, blo, bhi);
-  // the split element: widest by weight, else by raw range; none if every
-  // channel is constant over the node
-  int32_t ds = -1, dr = -1;
+// The element a node is split by: the widest by weight, else by raw range.
+template <int D, int S>
+__device__ __forceinline__ int32_t split_axis(const uint32_t *lo, const uint32_t *hi,
+                                              const uint32_t *wn, int32_t channels) {
+  int32_t ds = -1, dr = 0;
   uint64_t best_w = 0;
   uint32_t best_r = 0;
 #pragma unroll
-  for (int k = 0; k < E; ++k) {
-    if (k >= a.channels) continue;
-    const uint32_t r = s_hi[k] - s_lo[k];
-    const uint64_t wr = uint64_t(r) * r * ((a.wn[k >> 2] >> ((k & 3) * 8)) & 0xFFu);
+  for (int k = 0; k < kElems<D, S>; ++k) {
+    if (k >= channels) continue;
+    const uint32_t r = hi[k] - lo[k];
+    const uint64_t wr = uint64_t(r) * r * ((wn[k >> 2] >> ((k & 3) * 8)) & 0xFFu);
     if (wr > best_w) best_w = wr, ds = k;
     if (r > best_r) best_r = r, dr = k;
   }
-  if (ds < 0) ds = dr;
-  if (ds < 0) {
-    // texels equal in every channel: every query sees them at one distance,
-    // so the one of smallest raster index stands for all
-    uint32_t mk = 0xFFFFFFFFu;
-    for (uint32_t i = b + tid; i < b + c; i += NT) mk = min(mk, glb(a.keys_in)[i]);
-    if (tid < c) atomicMin(&s_key, mk);
-    __syncthreads();
-    if (tid == 0) {
-      store_tx<S>(a.tvals, b, blo);
-      glb(a.tkeys)[b] = s_key;
-      store_rec_link(a.nodes, tree_record_bytes(S), node, u32x2{b, 1u | kTreeLeaf});
-      glb(a.res)[blockIdx.x] = u32x2{0u, 0u};
-    }
-    return;
-  }
-  if (c <= kLeafMax || depth >= kMaxDepth - 1) {
-    for (uint32_t i = b + tid; i < b + c; i += NT) {
-      store_tx<S>(a.tvals, i, load_tx<S>(a.vals_in, i));
-      glb(a.tkeys)[i] = glb(a.keys_in)[i];
-    }
-    if (tid == 0) {
-      store_rec_link(a.nodes, tree_record_bytes(S), node, u32x2{b, c | kTreeLeaf});
-      glb(a.res)[blockIdx.x] = u32x2{0u, 0u};
-    }
-    return;
-  }
-  // split at s = lo + (hi - lo + 1) / 2: lo < s <= hi, so both sides hold
-  // texels (the box is tight).  One pass, NT texels per round: left texels
-  // fill [b, b + left) from the front, right ones [b + left, b + c) from the
-  // back (the order inside a node does not matter: ties are decided by the
-  // stored coordinate), so the left count is known at the end.
-  const uint32_t s = s_lo[ds] + (s_hi[ds] - s_lo[ds] + 1) / 2;
-  const uint32_t lane = tid & 63u, wave = tid >> 6;
-  uint32_t lbase = 0, rbase = 0;
-  for (uint32_t base = 0; base < c; base += NT) {
-    const uint32_t i = b + base + tid;
-    const bool valid = base + tid < c;
-    Tx<S> t;
-    uint32_t key = 0;
-    bool left = false;
-    if (valid) {
-      t = load_tx<S>(a.vals_in, i);
-      key = glb(a.keys_in)[i];
-      uint32_t v = 0;
-      for_elems<0, E>([&](auto k) {
-        constexpr int K = decltype(k)::value;
-        if (K == ds) v = elem<D, S, K>(t);
-      });
-      left = v < s;
-    }
-    const uint64_t bal = __ballot(left);
-    const uint32_t pre =
-        __builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u));
-    if (lane == 0) s_wave[wave] = uint32_t(__popcll(bal));
-    __syncthreads();
-    uint32_t woff = 0, tot = 0;
-#pragma unroll
-    for (uint32_t w = 0; w < NW; ++w) {
-      woff += w < wave ? s_wave[w] : 0u;
-      tot += s_wave[w];
-    }
-    if (valid) {
-      const uint32_t pl = woff + pre;  // left texels before this one in the round
-      const uint32_t dst = left ? b + lbase + pl : b + c - 1u - (rbase + (tid - pl));
-      store_tx<S>(a.vals_out, dst, t);
-      glb(a.keys_out)[dst] = key;
-    }
-    lbase += tot;
-    rbase += min(NT, c - base) - tot;
-    __syncthreads();
-  }
-  if (tid == 0) glb(a.res)[blockIdx.x] = u32x2{1u, lbase};
+  return ds < 0 ? dr : ds;
 }
 
-// Numbers the children of this level's split nodes in list order (one
-// workgroup of 1024 threads): child pair r of the level gets nodes
-// nnodes + 2r, + 2r + 1 and list entries 2r, 2r + 1.  ctr[0] = entries of
-// the next level, ctr[1] = nodes so far.
-__global__ void __launch_bounds__(1024) k_tree_alloc(const u32x4 *list_in, const u32x2 *res,
-                                                     uint32_t m, uint32_t nnodes, u32x4 *list_out,
-                                                     void *nodes, uint32_t rec_bytes,
-                                                     uint32_t *ctr) {
-  __shared__ uint32_t s_wave[16];
+// Element ds (not a compile-time constant) of a texel.
+template <int D, int S>
+__device__ __forceinline__ uint32_t elem_at(const Tx<S> &t, int32_t ds) {
+  constexpr int32_t kLog = D == 8 ? 2 : 1;  // elements per word
+  uint32_t w = t.w[0];
+#pragma unroll
+  for (int k = 1; k < S / 4; ++k) w = (ds >> kLog) == k ? t.w[k] : w;
+  return D == 8 ? (w >> ((ds & 3) * 8)) & 0xFFu : (w >> ((ds & 1) * 16)) & 0xFFFFu;
+}
+
+template <int D, int S>
+struct Box {
+  Pairs<D, S> lo, hi;
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int k = 0; k < kPairs<D, S>; ++k) lo.p[k] = u16x2{0xFFFF, 0xFFFF}, hi.p[k] = u16x2{0, 0};
+  }
+  __device__ __forceinline__ void add(const Pairs<D, S> &l, const Pairs<D, S> &h) {
+#pragma unroll
+    for (int k = 0; k < kPairs<D, S>; ++k) {
+      lo.p[k] = __builtin_elementwise_min(lo.p[k], l.p[k]);
+      hi.p[k] = __builtin_elementwise_max(hi.p[k], h.p[k]);
+    }
+  }
+  // joined with the box of lane ^ o
+  __device__ __forceinline__ void join(int32_t o) {
+    Pairs<D, S> l, h;
+#pragma unroll
+    for (int k = 0; k < kPairs<D, S>; ++k) {
+      l.p[k] = __builtin_bit_cast(u16x2, __shfl_xor(__builtin_bit_cast(int, lo.p[k]), o, 64));
+      h.p[k] = __builtin_bit_cast(u16x2, __shfl_xor(__builtin_bit_cast(int, hi.p[k]), o, 64));
+    }
+    add(l, h);
+  }
+  __device__ __forceinline__ void elems(uint32_t *l, uint32_t *h) const {
+    const Tx<S> tl = from_pairs<D, S>(lo), th = from_pairs<D, S>(hi);
+    for_elems<0, kElems<D, S>>([&](auto k) {
+      constexpr int K = decltype(k)::value;
+      l[K] = elem<D, S, K>(tl), h[K] = elem<D, S, K>(th);
+    });
+  }
+  // into a segment's box words, by one lane
+  __device__ __forceinline__ void widen(uint32_t *words) const {
+    uint32_t l[kElems<D, S>], h[kElems<D, S>];
+    elems(l, h);
+#pragma unroll
+    for (int k = 0; k < kElems<D, S>; ++k) {
+      atomicMin(words + k, l[k]);
+      atomicMin(words + kElems<D, S> + k, ~h[k]);
+    }
+  }
+};
+
+// Clears what the build accumulates into: `ones` words of all ones at a and
+// at b, zeros at c.
+__global__ void __launch_bounds__(256) k_tree_clear(uint32_t *a, uint32_t na, uint32_t *b,
+                                                    uint32_t nb, uint32_t *c, uint32_t nc) {
+  const uint32_t step = gridDim.x * 256u, first = blockIdx.x * 256u + threadIdx.x;
+  for (uint32_t i = first; i < na; i += step) glb(a)[i] = 0xFFFFFFFFu;
+  for (uint32_t i = first; i < nb; i += step) glb(b)[i] = 0xFFFFFFFFu;
+  for (uint32_t i = first; i < nc; i += step) glb(c)[i] = 0u;
+}
+
+// The whole guide's box.
+template <int D, int S>
+__global__ void __launch_bounds__(256) k_tree_box(const void *guide, uint32_t n, uint32_t *box) {
+  __shared__ uint32_t words[kBoxWords<D, S>];
+  const uint32_t tid = threadIdx.x;
+  if (tid < kBoxWords<D, S>) words[tid] = 0xFFFFFFFFu;
+  __syncthreads();
+  Box<D, S> b;
+  b.clear();
+  for (uint32_t i = blockIdx.x * 256u + tid; i < n; i += gridDim.x * 256u) {
+    const Pairs<D, S> p = to_pairs<D, S>(load_tx<S>(guide, i));
+    b.add(p, p);
+  }
+#pragma unroll
+  for (int32_t o = 1; o < 64; o <<= 1) b.join(o);
+  if ((tid & 63u) == 0) b.widen(words);
+  __syncthreads();
+  if (tid < kBoxWords<D, S>) atomicMin(box + tid, words[tid]);
+}
+
+// A level's segment of a workgroup (kSortBlock texels, so one segment) and
+// how it is split.
+template <int D, int S>
+struct Segment {
+  uint32_t id, first, count, half, lo;
+  int32_t axis, shift;
+  __device__ __forceinline__ explicit Segment(const SplitArgs &a) {
+    const uint32_t seg = blockIdx.x >> (a.lg - int32_t(kSortLog));
+    id = (1u << a.level) - 1u + seg;
+    first = seg << a.lg;
+    count = min(a.in.n - first, 1u << a.lg);
+    half = 1u << (a.lg - 1);
+    const SB_GLOBAL uint32_t *box = glb(a.boxes) + size_t(id) * kBoxWords<D, S>;
+    uint32_t l[kElems<D, S>], h[kElems<D, S>];
+#pragma unroll
+    for (int k = 0; k < kElems<D, S>; ++k) l[k] = box[k], h[k] = ~box[kElems<D, S> + k];
+    axis = split_axis<D, S>(l, h, a.wn, a.channels);
+    lo = 0;
+    uint32_t range = 0;
+#pragma unroll
+    for (int k = 0; k < kElems<D, S>; ++k)
+      if (k == axis) lo = l[k], range = h[k] - l[k];
+    const int32_t bits = 32 - __clz(int(range));
+    shift = max(bits - int32_t(kBinsLog), 0);
+  }
+  // a texel's bin: its value along the axis, in at most kBins steps
+  __device__ __forceinline__ uint32_t bin(const Tx<S> &t) const {
+    return (elem_at<D, S>(t, axis) - lo) >> shift;
+  }
+};
+
+constexpr uint32_t kSplitPer = kSortBlock / 256;
+
+// First half of a level's splits: the histogram of every segment's texels
+// along its axis.
+template <int D, int S>
+__global__ void __launch_bounds__(256) k_tree_hist(SplitArgs a) {
+  __shared__ uint32_t bins[kBins];
+  const Segment<D, S> sg(a);
+  if (sg.count <= sg.half) return;  // all of it goes left
+  const uint32_t tid = threadIdx.x;
+#pragma unroll
+  for (uint32_t k = 0; k < kBins; k += 256) bins[k + tid] = 0u;
+  __syncthreads();
+  const uint32_t i0 = blockIdx.x * kSortBlock + tid;
+  Tx<S> t[kSplitPer];
+#pragma unroll
+  for (uint32_t k = 0; k < kSplitPer; ++k)
+    t[k] = load_tx<S>(a.in.vals, min(i0 + 256 * k, a.in.n - 1));
+#pragma unroll
+  for (uint32_t k = 0; k < kSplitPer; ++k)
+    if (i0 + 256 * k < a.in.n) atomicAdd(&bins[sg.bin(t[k])], 1u);
+  __syncthreads();
+#pragma unroll
+  for (uint32_t k = 0; k < kBins; k += 256)
+    if (bins[k + tid] != 0u) atomicAdd(a.hist + size_t(sg.id) * kBins + k + tid, bins[k + tid]);
+}
+
+// Second half: the texels move to their child's range of the other buffer.
+// The median's bin is the one that the left child's last place falls in;
+// texels below it go left, above it right, and as many of the bin's own as
+// the left child has places for.  Places within a class are dealt to the
+// segment's workgroups by three counters (the tree's shape follows from the
+// guide up to the order of a bin's texels; a search's result does not depend
+// on it).  On the way the children's boxes are taken.
+template <int D, int S>
+__global__ void __launch_bounds__(256) k_tree_split(SplitArgs a) {
+  __shared__ uint32_t part[4], found[3], wave_n[4][3], base[3];
+  __shared__ uint32_t box[2 * kBoxWords<D, S>];
+  const Segment<D, S> sg(a);
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  uint32_t run = 0;
-  for (uint32_t base = 0; base < m; base += 1024) {
-    const uint32_t j = base + tid;
-    const bool split = j < m && glb(res)[j].x != 0u;
-    const uint64_t bal = __ballot(split);
-    const uint32_t pre =
-        __builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u));
-    if (lane == 0) s_wave[wave] = uint32_t(__popcll(bal));
+  if (tid < 2 * kBoxWords<D, S>) box[tid] = 0xFFFFFFFFu;
+  uint32_t mid = kBins, below = sg.count, same = 0u;  // all left
+  if (sg.count > sg.half) {
+    const SB_GLOBAL uint32_t *hist = glb(a.hist) + size_t(sg.id) * kBins;
+    uint32_t h[kBins / 256], sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kBins / 256; ++k) sum += h[k] = hist[(kBins / 256) * tid + k];
+    uint32_t incl = sum;
+#pragma unroll
+    for (uint32_t o = 1; o < 64; o <<= 1) {
+      const uint32_t v = uint32_t(__shfl_up(int(incl), o, 64));
+      if (lane >= o) incl += v;
+    }
+    if (lane == 63) part[wave] = incl;
     __syncthreads();
-    uint32_t woff = 0, tot = 0;
-    for (uint32_t w = 0; w < 16; ++w) {
-      woff += w < wave ? s_wave[w] : 0u;
-      tot += s_wave[w];
+    uint32_t run = incl - sum;
+    for (uint32_t w = 0; w < wave; ++w) run += part[w];
+#pragma unroll
+    for (uint32_t k = 0; k < kBins / 256; ++k) {
+      if (run <= sg.half && sg.half < run + h[k])
+        found[0] = (kBins / 256) * tid + k, found[1] = run, found[2] = h[k];
+      run += h[k];
     }
-    if (split) {
-      const uint32_t r = run + woff + pre, child = nnodes + 2 * r;
-      const u32x4 e = glb(list_in)[j];
-      const uint32_t lc = glb(res)[j].y;
-      store_rec_link(nodes, rec_bytes, e.z, u32x2{child, 0u});
-      glb(list_out)[2 * r] = u32x4{e.x, lc, child, 0u};
-      glb(list_out)[2 * r + 1] = u32x4{e.x + lc, e.y - lc, child + 1, 0u};
+    __syncthreads();
+    mid = found[0], below = found[1], same = found[2];
+  }
+  const uint32_t take = sg.half - min(below, sg.half);  // of the median's bin, to the left
+  const uint32_t i0 = blockIdx.x * kSortBlock + tid;
+  Tx<S> t[kSplitPer];
+  uint32_t key[kSplitPer], rank[kSplitPer], cls[kSplitPer], n[3] = {0u, 0u, 0u};
+#pragma unroll
+  for (uint32_t k = 0; k < kSplitPer; ++k) {
+    const uint32_t i = min(i0 + 256 * k, a.in.n - 1);
+    t[k] = load_tx<S>(a.in.vals, i);
+    key[k] = texel_key(a.in, i);
+  }
+  const uint64_t under = (1ull << lane) - 1ull;
+#pragma unroll
+  for (uint32_t k = 0; k < kSplitPer; ++k) {
+    const uint32_t b = sg.bin(t[k]);
+    // 0 below the median's bin, 1 in it, 2 above, 3 no texel
+    cls[k] = i0 + 256 * k >= a.in.n ? 3u : b < mid ? 0u : b == mid ? 1u : 2u;
+    rank[k] = 0u;
+#pragma unroll
+    for (uint32_t c = 0; c < 3; ++c) {
+      const uint64_t m = __ballot(cls[k] == c);
+      if (cls[k] == c) rank[k] = n[c] + uint32_t(__popcll(m & under));
+      n[c] += uint32_t(__popcll(m));
     }
-    run += tot;
+  }
+  if (lane < 3) wave_n[wave][lane] = lane == 0 ? n[0] : lane == 1 ? n[1] : n[2];
+  __syncthreads();
+  if (tid < 3)
+    base[tid] = atomicAdd(a.ctr + size_t(sg.id) * 4 + tid,
+                          wave_n[0][tid] + wave_n[1][tid] + wave_n[2][tid] + wave_n[3][tid]);
+  __syncthreads();
+  uint32_t at[3];
+#pragma unroll
+  for (uint32_t c = 0; c < 3; ++c) {
+    at[c] = base[c];
+    for (uint32_t w = 0; w < wave; ++w) at[c] += wave_n[w][c];
+  }
+  Box<D, S> left, right;
+  left.clear();
+  right.clear();
+#pragma unroll
+  for (uint32_t k = 0; k < kSplitPer; ++k) {
+    if (cls[k] == 3u) continue;
+    const uint32_t r = rank[k] + (cls[k] == 0u ? at[0] : cls[k] == 1u ? at[1] : at[2]);
+    const bool l = cls[k] == 0u || (cls[k] == 1u && r < take);
+    const uint32_t place = cls[k] == 0u   ? r
+                           : cls[k] == 1u ? (l ? below + r : sg.half + (r - take))
+                                          : sg.half + (same - take) + r;
+    store_tx<S>(a.vals_out, sg.first + place, t[k]);
+    glb(a.keys_out)[sg.first + place] = key[k];
+    const Pairs<D, S> p = to_pairs<D, S>(t[k]);
+    if (l) left.add(p, p);
+    else right.add(p, p);
+  }
+  if (a.last) return;
+#pragma unroll
+  for (int32_t o = 1; o < 64; o <<= 1) left.join(o), right.join(o);
+  if (lane == 0) {
+    left.widen(box);
+    right.widen(box + kBoxWords<D, S>);
+  }
+  __syncthreads();
+  // the segment's children are neighbours in the next level
+  if (tid < 2 * kBoxWords<D, S>)
+    atomicMin(a.boxes + size_t(2u * sg.id + 1u) * kBoxWords<D, S> + tid, box[tid]);
+}
+
+struct SortArgs {
+  TexelsIn in;
+  void *recs;
+  uint32_t *keys;
+  int32_t levels;
+  uint32_t wn[2];
+  int32_t channels;
+};
+
+// The last kSortLog - 3 splits of kSortBlock texels, in LDS: at every size
+// 2^lg the block's segments take their boxes and axes and are sorted along
+// them (bitonic, on value << kSortLog | texel), which leaves each segment's
+// halves split at the median; then the texels' entries and those of the
+// three levels above them are written.  A wave's threads own 256 places,
+// so a sort's exchanges within 256 places need no barrier.
+template <int D, int S>
+__global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
+  __shared__ Tx<S> tex[kSortBlock];
+  __shared__ __attribute__((aligned(16))) uint32_t ky[kSortBlock];
+  __shared__ Box<D, S> wbox[8];
+  __shared__ uint32_t wkey[8];
+  constexpr uint32_t kNone = 0xFFFFFFFFu;  // past the last texel: sorts behind every one
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t first = blockIdx.x * kSortBlock, count = min(a.in.n - first, kSortBlock);
+#pragma unroll
+  for (uint32_t k = 0; k < kSortBlock; k += 512) {
+    const uint32_t i = k + tid;
+    if (i < count) tex[i] = load_tx<S>(a.in.vals, first + i);
+    ky[i] = i < count ? i : kNone;
+  }
+  __syncthreads();
+  for (uint32_t lg = kSortLog; lg >= 4; --lg) {
+    uint32_t own[4];
+    Box<D, S> b;
+    b.clear();
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      own[j] = ky[4 * tid + j];
+      if (own[j] != kNone) {
+        own[j] &= kSortBlock - 1u;
+        const Pairs<D, S> p = to_pairs<D, S>(tex[own[j]]);
+        b.add(p, p);
+      }
+    }
+    for (int32_t o = 1; o < 64 && uint32_t(4 * o) < (1u << lg); o <<= 1) b.join(o);
+    if (lg > 8) {  // the segment's waves
+      if (lane == 0) wbox[wave] = b;
+      __syncthreads();
+      const uint32_t nw = 1u << (lg - 8), w0 = wave & ~(nw - 1u);
+      for (uint32_t w = 0; w < nw; ++w) b.add(wbox[w0 + w].lo, wbox[w0 + w].hi);
+    }
+    uint32_t l[kElems<D, S>], h[kElems<D, S>];
+    b.elems(l, h);
+    const int32_t axis = split_axis<D, S>(l, h, a.wn, a.channels);
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j)
+      if (own[j] != kNone)
+        ky[4 * tid + j] = (elem_at<D, S>(tex[own[j]], axis) << kSortLog) | own[j];
+    // pairs 128 wave + lane and + 64: places of the wave's own 256 while a
+    // pair block holds at most 128 pairs
+    bool wide = false;
+    auto exchange = [&](uint32_t half, uint32_t flip) {
+      const bool w = half > 128u;
+      if (w || wide) __syncthreads();
+      else wave_lds_sync();
+      wide = w;
+#pragma unroll
+      for (uint32_t u = 0; u < 128; u += 64) {
+        const uint32_t p = 128u * wave + u + lane;
+        const uint32_t i = ((p & ~(half - 1u)) << 1) | (p & (half - 1u)), o = i ^ flip;
+        const uint32_t x = ky[i], y = ky[o];
+        ky[i] = min(x, y), ky[o] = max(x, y);
+      }
+    };
+    for (uint32_t k = 2; k <= (1u << lg); k <<= 1) {
+      exchange(k >> 1, k - 1u);
+      for (uint32_t j = k >> 2; j > 0; j >>= 1) exchange(j, j);
+    }
+    wave_lds_sync();
+  }
+  Box<D, S> b;
+  b.clear();
+  uint32_t mk = kNoTreeKey;
+#pragma unroll
+  for (uint32_t j = 0; j < 4; ++j) {
+    const uint32_t v = ky[4 * tid + j];
+    if (v == kNone) continue;
+    const Tx<S> t = tex[v & (kSortBlock - 1u)];
+    const uint32_t key = texel_key(a.in, first + (v & (kSortBlock - 1u)));
+    const uint32_t e = tree_start(a.levels) + first + 4 * tid + j;
+    store_rec<S>(a.recs, e, t, t);
+    glb(a.keys)[e] = key;
+    const Pairs<D, S> p = to_pairs<D, S>(t);
+    b.add(p, p);
+    mk = min(mk, key);
+  }
+  // node p of the level `up` above the texels, where it exists
+  auto node = [&](int32_t up, uint32_t p) {
+    if (up >= a.levels || mk == kNoTreeKey) return;
+    const uint32_t e = tree_start(a.levels - up) + p;
+    store_rec<S>(a.recs, e, from_pairs<D, S>(b.lo), from_pairs<D, S>(b.hi));
+    glb(a.keys)[e] = mk;
+  };
+#pragma unroll
+  for (int32_t o = 1; o < 64; o <<= 1) {
+    b.join(o);
+    mk = min(mk, uint32_t(__shfl_xor(int(mk), o, 64)));
+    if (o == 1 && (lane & 1u) == 0) node(1, (first + 4 * tid) >> 3);
+    if (o == 8 && (lane & 15u) == 0) node(2, (first + 4 * tid) >> 6);
+  }
+  if (lane == 0) wbox[wave] = b, wkey[wave] = mk;
+  __syncthreads();
+  if (lane == 0 && (wave & 1u) == 0) {
+    b.add(wbox[wave + 1].lo, wbox[wave + 1].hi);
+    mk = min(mk, wkey[wave + 1]);
+    node(3, (first + 4 * tid) >> 9);
+  }
+}
+
+// The levels above k_tree_sort's (one workgroup: at most 2^17 nodes' records
+// are read), and the header.
+template <int D, int S>
+__global__ void __launch_bounds__(1024) k_tree_top(void *recs, uint32_t *keys, int32_t levels,
+                                                   uint32_t n, uint32_t *header,
+                                                   uint32_t channels) {
+  for (int32_t up = 4; up < levels; ++up) {
+    const uint32_t kids = uint32_t((uint64_t(n) + (1ull << (3 * up - 3)) - 1) >> (3 * up - 3));
+    const uint32_t from = tree_start(levels - up + 1), to = tree_start(levels - up);
+    for (uint32_t i = threadIdx.x; 8u * i < kids; i += 1024) {
+      Box<D, S> b;
+      b.clear();
+      uint32_t mk = kNoTreeKey;
+      for (uint32_t c = 8 * i; c < min(8 * i + 8, kids); ++c) {
+        Tx<S> lo, hi;
+        load_recs<S, 1>(recs, from + c, &lo, &hi);
+        b.add(to_pairs<D, S>(lo), to_pairs<D, S>(hi));
+        mk = min(mk, glb(keys)[from + c]);
+      }
+      store_rec<S>(recs, to + i, from_pairs<D, S>(b.lo), from_pairs<D, S>(b.hi));
+      glb(keys)[to + i] = mk;
+    }
     __syncthreads();
   }
-  if (tid == 0) {
-    glb(ctr)[0] = 2 * run;
-    glb(ctr)[1] = nnodes + 2 * run;
+  // header: entries, texels, texel bytes, channels (for inspection only)
+  if (threadIdx.x == 0) {
+    glb(header)[0] = tree_start(levels) + n;
+    glb(header)[1] = n;
+    glb(header)[2] = S;
+    glb(header)[3] = channels;
   }
 }
 
 // ------------------------------------------------------------- frame passes
 
 __device__ inline TreeView frame_tree(const FrameArgs &a) {
-  return TreeView{a.t_nodes, a.t_vals, a.t_keys};
+  return TreeView{a.t_recs, a.t_keys, a.t_levels};
 }
 
 // Record idx of the padded seed table: the seed of its cell and the
-// translation u* - q of the seed's search.
+// translation u* - q of the seed's search, eight lanes per record (too few
+// records to fill the chip with fewer lanes each, and the pass takes as long
+// as its longest search).
 template <int D, int S>
 __global__ void __launch_bounds__(256) k_seeds_n(FrameArgs a) {
-  // eight lanes per record, each searching part of the tree
+  extern __shared__ uint32_t stack[];
   const uint32_t idx = (blockIdx.x * 256 + threadIdx.x) >> 3, g = threadIdx.x & 7u;
   const Levels &lv = a.lv;
   if (idx >= uint32_t(lv.poffset[lv.count])) return;
@@ -661,7 +887,7 @@ __global__ void __launch_bounds__(256) k_seeds_n(FrameArgs a) {
     if (sx < uint32_t(a.w) && sy < uint32_t(a.h)) {
       const uint32_t at = __umul24(sy, uint32_t(a.w)) + sx;
       const uint32_t u =
-          tree_search_group8<D, S>(frame_tree(a), load_tx<S>(a.tgt_guide, at), a.wn, g);
+          tree_search<D, S, 8>(frame_tree(a), load_tx<S>(a.tgt_guide, at), a.wn, stack);
       rec.x = pack_xy(4 * sx, 4 * sy);
       rec.y = pack_off(int32_t(u & 0xFFFFu) - int32_t(sx), int32_t(u >> 16) - int32_t(sy));
     }
@@ -724,46 +950,92 @@ __global__ void __launch_bounds__(256) k_assign_n(FrameArgs a) {
   }
 }
 
-// The own lookups of the pixels no level accepted (fallback chunk code),
-// one thread per pixel of 16 x 16 tiles, each wave an 8 x 8 quarter of its
-// tile (neighbours' searches take similar paths and lengths), so a region
-// where most pixels fall back has every lane searching once rather than a
-// few lanes searching in turn.  The search starts from the candidate the
-// level loop left in the vote-distance slot (its distance measured again
-// here), then the slot takes the result's vote distance.
-template <int D, int S>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
-    k_fallback_n(FrameArgs a) {
+// The own lookups of the pixels no level accepted (fallback chunk code): a
+// 16 x 16 tile lists them in LDS (each wave an 8 x 8 quarter: neighbours'
+// searches take similar paths) and its groups of G lanes take them in turn,
+// a group starting its next search as soon as its last one ends.  A search
+// starts from the candidate the level loop left in the vote-distance slot
+// (its distance measured again here), then the slot takes the result's vote
+// distance.
+template <int D, int S, int G>
+__global__ void __launch_bounds__(256) k_fallback_n(FrameArgs a) {
   typedef typename DistOf<D>::type Dist;
+  extern __shared__ uint32_t stack[];
+  __shared__ uint8_t list[256];
+  __shared__ uint32_t count;
+  const uint32_t tid = threadIdx.x;
   const uint32_t tiles_x = (uint32_t(a.w) + 15u) / 16u;
   const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
-  const uint32_t wq = threadIdx.x >> 6, ln = threadIdx.x & 63u;
-  const int32_t x = int32_t((tile % tiles_x) * 16u + (wq & 1u) * 8u + (ln & 7u));
-  const int32_t y = int32_t((tile / tiles_x) * 16u + (wq >> 1) * 8u + (ln >> 3));
-  if (x >= a.w || y >= a.h) return;
-  const uint32_t pidx = __umul24(uint32_t(y), uint32_t(a.w)) + uint32_t(x);
-  if ((glb(a.out_chunk)[pidx] >> 26) != uint32_t(a.lv.count)) return;
-  const uint32_t ckey = glb(a.offsets)[pidx];
-  const Tx<S> gt = load_tx<S>(a.tgt_guide, pidx);
-  Dist cd = ~Dist(0);
-  if (ckey != 0xFFFFFFFFu) {
-    const uint32_t cidx = __umul24(ckey >> 16, uint32_t(a.sw)) + (ckey & 0xFFFFu);
-    cd = tx_dist<D, S>(gt, load_tx<S>(a.src_guide, cidx), a.wn);
+  const uint32_t x0 = (tile % tiles_x) * 16u, y0 = (tile / tiles_x) * 16u;
+  // pixel t of the tile
+  auto px = [&](uint32_t t) { return x0 + ((t >> 6) & 1u) * 8u + (t & 7u); };
+  auto py = [&](uint32_t t) { return y0 + (t >> 7) * 8u + ((t >> 3) & 7u); };
+  if (tid == 0) count = 0u;
+  __syncthreads();
+  bool need = px(tid) < uint32_t(a.w) && py(tid) < uint32_t(a.h);
+  if (need)
+    need = (glb(a.out_chunk)[__umul24(py(tid), uint32_t(a.w)) + px(tid)] >> 26) ==
+           uint32_t(a.lv.count);
+  const uint64_t bal = __ballot(need);
+  uint32_t base = 0;
+  if ((tid & 63u) == 0 && bal != 0) base = atomicAdd(&count, uint32_t(__popcll(bal)));
+  base = __builtin_amdgcn_readfirstlane(base);
+  const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+      uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u));
+  if (need) list[base + below] = uint8_t(tid);
+  __syncthreads();
+  const uint32_t n = count;
+  uint32_t e = tid / G;
+  if (e >= n) return;
+  const TreeView tv = frame_tree(a);
+  const Weights<D, S> wt(a.wn);
+  uint32_t *slots = lane_slots<G>(tv, stack);
+  Search<D, S, G> s;
+  uint32_t x, y, pidx;
+  auto begin = [&]() {
+    x = px(list[e]), y = py(list[e]);
+    pidx = __umul24(y, uint32_t(a.w)) + x;
+    const uint32_t ckey = glb(a.offsets)[pidx];
+    const Tx<S> gt = load_tx<S>(a.tgt_guide, pidx);
+    Dist cd = ~Dist(0);
+    if (ckey != 0xFFFFFFFFu) {
+      const uint32_t cidx = __umul24(ckey >> 16, uint32_t(a.sw)) + (ckey & 0xFFFFu);
+      cd = tx_dist<D, S>(gt, load_tx<S>(a.src_guide, cidx), a.wn);
+    }
+    s.start(gt, cd, ckey);
+  };
+  begin();
+  for (;;) {
+    if (!s.step(tv, wt, slots)) continue;
+    if ((tid & uint32_t(G - 1)) == 0) {
+      const uint32_t u = s.best_key;
+      const uint32_t off =
+          pack_off(int32_t(u & 0xFFFFu) - int32_t(x), int32_t(u >> 16) - int32_t(y));
+      glb(a.offsets)[pidx] = vote_distance(a, off);
+      if (a.out_nnf) glb(a.out_nnf)[pidx] = u;
+    }
+    e += 256u / G;
+    if (e >= n) break;
+    begin();
   }
-  const uint32_t u = tree_search<D, S>(frame_tree(a), gt, a.wn, cd, ckey);
-  const uint32_t off = pack_off(int32_t(u & 0xFFFFu) - x, int32_t(u >> 16) - y);
-  glb(a.offsets)[pidx] = vote_distance(a, off);
-  if (a.out_nnf) glb(a.out_nnf)[pidx] = u;
 }
 
-template <int D, int S>
+// G lanes per query texel.
+template <int D, int S, int G>
 __global__ void __launch_bounds__(256) k_tree_query(TreeView tv, const void *q, uint32_t n,
                                                     uint32_t *out, uint32_t w0, uint32_t w1) {
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  extern __shared__ uint32_t stack[];
+  const uint64_t i = (uint64_t(blockIdx.x) * 256 + threadIdx.x) / G;
   if (i >= n) return;
   const uint32_t wn[2] = {w0, w1};
-  glb(out)[i] = tree_search<D, S>(tv, load_tx<S>(q, i), wn);
+  const uint32_t u = tree_search<D, S, G>(tv, load_tx<S>(q, uint32_t(i)), wn, stack);
+  if ((threadIdx.x & uint32_t(G - 1)) == 0) glb(out)[i] = u;
 }
+
+// Lanes per search of the fallback pass, and up to how many queries eight
+// lanes take one rather than four.
+constexpr int kFallbackLanes = 4;
+constexpr int64_t kQueryWide = 65536;
 
 // ------------------------------------------------------------------- host
 
@@ -789,35 +1061,42 @@ unsigned blocks_for(uint64_t n, unsigned bs) { return unsigned((n + bs - 1) / bs
 
 bool side_ok(int32_t v) { return v >= 1 && v <= SB_MAX_SIDE; }
 
+// The build's workspace: the texels and keys of two consecutive levels of
+// splits, and per segment of the levels split over the chip its box, its
+// histogram and its counters.
 struct BuildWs {
   void *vals[2];
   uint32_t *keys[2];
-  u32x4 *list[2];
-  u32x2 *res;
-  uint32_t *ctr;
+  uint32_t *boxes, *hist, *ctr;
+  uint32_t box_words, hist_words;  // hist and ctr together
+  int32_t splits;                  // levels split over the chip
   size_t total;
 };
 
-BuildWs build_ws(char *base, size_t n, size_t t) {
+BuildWs build_ws(char *base, size_t n, size_t t, size_t box_words) {
   BuildWs w;
+  w.splits = 0;
+  while ((size_t(kSortBlock) << w.splits) < n) ++w.splits;
+  const size_t segs = (size_t(1) << w.splits) - 1;  // at most n / 1024
   size_t at = 0;
-  for (int k = 0; k < 2; ++k) {
-    w.vals[k] = base ? base + at : nullptr;
-    at += align256(n * t);
-  }
-  for (int k = 0; k < 2; ++k) {
-    w.keys[k] = base ? reinterpret_cast<uint32_t *>(base + at) : nullptr;
-    at += align256(n * 4);
-  }
-  for (int k = 0; k < 2; ++k) {
-    w.list[k] = base ? reinterpret_cast<u32x4 *>(base + at) : nullptr;
-    at += align256(n * 16);
-  }
-  w.res = base ? reinterpret_cast<u32x2 *>(base + at) : nullptr;
-  at += align256(n * 8);
-  w.ctr = base ? reinterpret_cast<uint32_t *>(base + at) : nullptr;
-  at += 256;
+  auto take = [&](size_t bytes) {
+    char *p = base ? base + at : nullptr;
+    at += align256(bytes);
+    return p;
+  };
+  for (int k = 0; k < 2; ++k) w.vals[k] = take(n * t);
+  for (int k = 0; k < 2; ++k) w.keys[k] = reinterpret_cast<uint32_t *>(take(n * 4));
+  // 40 bytes per texel for the segments' data, which need less than 5
+  char *seg = take(n * 16);
+  take(n * 16);
+  take(n * 8);
+  take(256);
   w.total = at;
+  w.box_words = uint32_t(segs * box_words);
+  w.hist_words = uint32_t(segs * (kBins + 4));
+  w.boxes = reinterpret_cast<uint32_t *>(seg);
+  w.hist = w.boxes + w.box_words;
+  w.ctr = w.hist + segs * kBins;
   return w;
 }
 
@@ -841,14 +1120,17 @@ hipError_t launch_search_frame(const FrameArgs &a, hipEvent_t *ev, hipStream_t s
                          ((uint32_t(a.h) + kAssignTH - 1) / kAssignTH);
   return with_format(a.fmt, a.texel, [&](auto d, auto s) -> hipError_t {
     constexpr int D = decltype(d)::value, S = decltype(s)::value;
-    if (records > 0) k_seeds_n<D, S><<<blocks_for(uint64_t(records) * 8, 256), 256, 0, stream>>>(a);
+    if (records > 0)
+      k_seeds_n<D, S><<<blocks_for(uint64_t(records) * 8, 256), 256, stack_bytes<8>(a.t_levels),
+                        stream>>>(a);
     if (ev) {
       const hipError_t e = hipEventRecord(ev[1], stream);
       if (e != hipSuccess) return e;
     }
     k_assign_n<D, S><<<tiles, 256, 0, stream>>>(a);
     const uint32_t ftiles = ((uint32_t(a.w) + 15u) / 16u) * ((uint32_t(a.h) + 15u) / 16u);
-    k_fallback_n<D, S><<<ftiles, 256, 0, stream>>>(a);
+    k_fallback_n<D, S, kFallbackLanes>
+        <<<ftiles, 256, stack_bytes<kFallbackLanes>(a.t_levels), stream>>>(a);
     return hipGetLastError();
   });
 }
@@ -870,7 +1152,7 @@ size_t sb_tree_bytes(int32_t fmt, int32_t channels, int32_t sw, int32_t sh) {
 size_t sb_tree_workspace_bytes(int32_t fmt, int32_t channels, int32_t sw, int32_t sh) {
   const int32_t t = search_texel_bytes(fmt, channels);
   if (t == 0 || !side_ok(sw) || !side_ok(sh)) return 0;
-  return build_ws(nullptr, size_t(sw) * size_t(sh), size_t(t)).total;
+  return build_ws(nullptr, size_t(sw) * size_t(sh), size_t(t), 0).total;
 }
 
 int sb_tree_build(const void *guide, int32_t fmt, int32_t channels, int32_t sw, int32_t sh,
@@ -883,52 +1165,47 @@ int sb_tree_build(const void *guide, int32_t fmt, int32_t channels, int32_t sw, 
   const uint32_t n = uint32_t(sw) * uint32_t(sh);
   const TreeLayout l = tree_layout(n, size_t(t));
   if (tree_bytes < l.total) return SB_ENOMEM;
-  const BuildWs ws = build_ws(static_cast<char *>(workspace), n, size_t(t));
+  const BuildWs ws = build_ws(static_cast<char *>(workspace), n, size_t(t),
+                              2 * size_t(t) * 8 / size_t(fmt_depth(fmt)));
   if (workspace_bytes < ws.total) return SB_ENOMEM;
   char *tb = static_cast<char *>(tree);
-  BuildArgs a;
-  memset(&a, 0, sizeof a);
-  a.nodes = tb + l.nodes;
-  a.tvals = tb + l.vals;
-  a.tkeys = reinterpret_cast<uint32_t *>(tb + l.keys);
-  a.res = ws.res;
-  a.wn[0] = wn[0];
-  a.wn[1] = wn[1];
-  a.channels = channels;
+  uint32_t *keys = reinterpret_cast<uint32_t *>(tb + l.keys);
   hipError_t e = with_format(fmt, t, [&](auto d, auto s) -> hipError_t {
     constexpr int D = decltype(d)::value, S = decltype(s)::value;
-    k_tree_init<S><<<blocks_for(n, 256), 256, 0, stream>>>(guide, n, uint32_t(sw), ws.vals[0],
-                                                          ws.keys[0], ws.list[0]);
-    uint32_t m = 1, nnodes = 1;
-    int cur = 0;
-    for (int32_t depth = 0; m > 0; ++depth) {
-      if (depth >= kMaxDepth) return hipErrorUnknown;  // every node at the limit is a leaf
-      a.list_in = ws.list[cur];
-      a.vals_in = ws.vals[cur];
-      a.keys_in = ws.keys[cur];
-      a.vals_out = ws.vals[cur ^ 1];
-      a.keys_out = ws.keys[cur ^ 1];
-      // large nodes (the top levels) take 1024 threads each
-      if (uint64_t(m) * 16384u <= uint64_t(n))
-        k_tree_level<D, S, 1024><<<m, 1024, 0, stream>>>(a, depth);
-      else
-        k_tree_level<D, S, 256><<<m, 256, 0, stream>>>(a, depth);
-      k_tree_alloc<<<1, 1024, 0, stream>>>(ws.list[cur], ws.res, m, nnodes, ws.list[cur ^ 1],
-                                           a.nodes, uint32_t(tree_record_bytes(S)), ws.ctr);
-      uint32_t hc[2] = {0u, 0u};
-      hipError_t ec = hipMemcpyAsync(hc, ws.ctr, sizeof hc, hipMemcpyDeviceToHost, stream);
-      if (ec == hipSuccess) ec = hipStreamSynchronize(stream);
-      if (ec != hipSuccess) return ec;
-      m = hc[0];
-      nnodes = hc[1];
-      cur ^= 1;
+    const unsigned nblk = blocks_for(n, kSortBlock);
+    const uint64_t most = l.entries > ws.hist_words ? l.entries : ws.hist_words;
+    k_tree_clear<<<blocks_for(most, 256) < 2048 ? blocks_for(most, 256) : 2048, 256, 0, stream>>>(
+        keys, l.entries, ws.boxes, ws.box_words, ws.hist, ws.hist_words);
+    TexelsIn in = {guide, nullptr, n, uint32_t(sw)};
+    if (ws.splits > 0)
+      k_tree_box<D, S><<<nblk < 512 ? nblk : 512, 256, 0, stream>>>(guide, n, ws.boxes);
+    for (int32_t lv = 0; lv < ws.splits; ++lv) {
+      SplitArgs a;
+      a.in = in;
+      a.vals_out = ws.vals[lv & 1];
+      a.keys_out = ws.keys[lv & 1];
+      a.boxes = ws.boxes;
+      a.hist = ws.hist;
+      a.ctr = ws.ctr;
+      a.level = lv;
+      a.lg = int32_t(kSortLog) + ws.splits - lv;
+      a.last = lv + 1 == ws.splits;
+      a.wn[0] = wn[0];
+      a.wn[1] = wn[1];
+      a.channels = channels;
+      k_tree_hist<D, S><<<nblk, 256, 0, stream>>>(a);
+      k_tree_split<D, S><<<nblk, 256, 0, stream>>>(a);
+      in.vals = a.vals_out;
+      in.keys = a.keys_out;
     }
-    // header: nodes, texels, texel bytes, channels (for inspection only)
-    uint32_t hdr[4] = {nnodes, n, uint32_t(t), uint32_t(channels)};
-    hipError_t ec = hipMemcpyAsync(tb, hdr, sizeof hdr, hipMemcpyHostToDevice, stream);
-    if (ec == hipSuccess) ec = hipStreamSynchronize(stream);
+    const SortArgs a = {in, tb + l.recs, keys, l.levels, {wn[0], wn[1]}, channels};
+    k_tree_sort<D, S><<<nblk, 512, 0, stream>>>(a);
+    k_tree_top<D, S><<<1, 1024, 0, stream>>>(tb + l.recs, keys, l.levels, n,
+                                             reinterpret_cast<uint32_t *>(tb), uint32_t(channels));
+    const hipError_t ec = hipGetLastError();
     if (ec != hipSuccess) return ec;
-    return hipGetLastError();
+    // returns with the tree complete and the workspace idle
+    return hipStreamSynchronize(stream);
   });
   if (e != hipSuccess) {
     set_hip_error(e, "sb_tree_build");
@@ -949,8 +1226,12 @@ int sb_tree_query(const sb_style *style, const void *queries, int64_t n, uint32_
   const TreeView tv = tree_view(style->tree, size_t(style->sw) * size_t(style->sh), size_t(t));
   hipError_t e = with_format(style->fmt, t, [&](auto d, auto s) -> hipError_t {
     constexpr int D = decltype(d)::value, S = decltype(s)::value;
-    k_tree_query<D, S><<<blocks_for(uint64_t(n), 256), 256, 0, stream>>>(tv, queries, uint32_t(n),
-                                                                        out, wn[0], wn[1]);
+    if (n <= kQueryWide)
+      k_tree_query<D, S, 8><<<blocks_for(uint64_t(n) * 8, 256), 256, stack_bytes<8>(tv.levels),
+                              stream>>>(tv, queries, uint32_t(n), out, wn[0], wn[1]);
+    else
+      k_tree_query<D, S, 4><<<blocks_for(uint64_t(n) * 4, 256), 256, stack_bytes<4>(tv.levels),
+                              stream>>>(tv, queries, uint32_t(n), out, wn[0], wn[1]);
     return hipGetLastError();
   });
   if (e != hipSuccess) {
@@ -967,9 +1248,9 @@ namespace sb {
 void fill_tree_args(const sb_style *style, FrameArgs *a) {
   const int32_t t = search_texel_bytes(style->fmt, style->channels);
   const TreeView tv = tree_view(style->tree, size_t(style->sw) * size_t(style->sh), size_t(t));
-  a->t_nodes = tv.nodes;
-  a->t_vals = tv.vals;
+  a->t_recs = tv.recs;
   a->t_keys = tv.keys;
+  a->t_levels = tv.levels;
   a->texel = t;
   resolve_weights_n(style->weights, style->channels, a->wn);
 }

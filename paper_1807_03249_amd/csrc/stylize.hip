@@ -162,11 +162,6 @@ __global__ void __launch_bounds__(256) k_seeds(FrameArgs a) {
   seeds_body<FMT>(a, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // Records staged per wave: level i's nine at [kRecStride * i, + 9) of each
 // block's record array (its 3 x 3 neighbourhood, x outer, y inner).
 constexpr int32_t kRecStride = 12;
