@@ -232,16 +232,15 @@ int sb_style_destroy(sb_style *style);
  *   u*(g) = argmin_u sum_k w_k (g_k - G_S[u]_k)^2, ties to the smallest
  *   raster index of u,
  * over the raw channel values (no quantisation), with the style's weights.
- * The search runs on a k-d tree of the source guide built on the device:
- * every node holds the tight bounding box of its texels, inner nodes split
- * the widest (weighted) channel at the middle of the box, leaves hold at
- * most 8 texels (texels equal in every weighted channel collapse to the one
- * of smallest raster index), and a search skips a subtree only when its box
- * lies strictly farther than the best texel found, so the result is the
- * exact argmin for any tree shape.  Per frame: a seed pass searches each
- * seed's lookup (eight lanes per seed, over disjoint subtrees); the level
+ * The search runs on a balanced k-d tree of the source guide built on the
+ * device: eight children per node, every child with the tight bounding box of
+ * its texels and its smallest raster index, splits at the median of the widest
+ * (weighted) channel.  A search skips a child only when its box lies strictly
+ * farther than the best texel found, or as far with no smaller raster index
+ * in it, so the result is the exact argmin for any tree shape.  Per frame: a
+ * seed pass searches each seed's lookup (eight lanes per seed); the level
  * loop then runs as for the table formats, and a pass of its own searches
- * the own lookup of every pixel no level accepts (one thread per pixel,
+ * the own lookup of every pixel no level accepts (two lanes per pixel,
  * starting from the nearest candidate its level loop measured); the vote is
  * unchanged.  Not available with labels.  In a batch (sb_batch_run) such
  * frames run through the per-frame kernels after the batch kernels, on the
@@ -251,8 +250,8 @@ int sb_style_destroy(sb_style *style);
  * SB_GUIDE_U16XN: the smallest of 4, 8, 16 that holds the channels; 0 if
  * the pair is invalid. */
 int32_t sb_texel_bytes(int32_t fmt, int32_t channels);
-/* Bytes of the search tree of an Sw x Sh source (an upper bound: the tree
- * has at most 2 Sw Sh - 1 nodes); 0 on invalid arguments. */
+/* Bytes of the buffer for the search tree of an Sw x Sh source (an upper
+ * bound); 0 on invalid arguments. */
 size_t sb_tree_bytes(int32_t fmt, int32_t channels, int32_t sw, int32_t sh);
 /* Device workspace of sb_tree_build. */
 size_t sb_tree_workspace_bytes(int32_t fmt, int32_t channels, int32_t sw, int32_t sh);
@@ -263,9 +262,7 @@ size_t sb_tree_workspace_bytes(int32_t fmt, int32_t channels, int32_t sw, int32_
  *             weights, the style's weights decide the lookups
  *   tree      [device] sb_tree_bytes() bytes; workspace [device] of
  *             sb_tree_workspace_bytes()
- * Builds one tree level per round of launches and reads each level's node
- * count back, so it synchronises `stream` (and returns after the tree is
- * complete).  SB_EINVAL / SB_ENOMEM on bad arguments or small buffers,
+ * Synchronises `stream`: it returns after the tree is complete.  SB_EINVAL / SB_ENOMEM on bad arguments or small buffers,
  * SB_EHIP if a launch or copy fails. */
 int sb_tree_build(const void *guide, int32_t fmt, int32_t channels, int32_t sw, int32_t sh,
                   const uint8_t *weights, void *tree, size_t tree_bytes, void *workspace,

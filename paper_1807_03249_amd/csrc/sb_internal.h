@@ -56,12 +56,12 @@ __host__ __device__ constexpr int32_t search_texel_bytes(int32_t fmt, int32_t ch
 // 8-ary tree of `levels` levels below the root, the smallest number with
 // 8^levels >= n, in level order: node p of level d is entry tree_start(d) +
 // p, its children the entries 8 p .. 8 p + 7 of level d + 1, and the entries
-// of the last level are the texels.  An entry is a record of 2t bytes -- the
-// node's box, the lowest and the highest value of every element over its
-// texels, as two texels (both the texel itself on the last level) -- and a
-// key, the smallest source coordinate (x | y << 16 as y << 16 | x orders like
-// the raster index) of its texels; kNoTreeKey marks the entries past a level's
-// last node, up to a multiple of eight.  Records, then keys, in one buffer.
+// of the last level are the texels.  Three sections: per node above the last
+// but one level its children's boxes, the eight lowest values of every
+// element and then the eight highest (16 texels); the texels; and per entry a
+// key, the smallest source coordinate (x | y << 16: y << 16 | x orders like
+// the raster index) of its texels, kNoTreeKey for the entries past a level's
+// last node, up to a multiple of eight.
 constexpr uint32_t kNoTreeKey = 0xFFFFFFFFu;
 __host__ __device__ constexpr uint32_t tree_start(int32_t d) {
   return 0x49249249u & ((1u << (3 * d)) - 1u);  // (8^d - 1) / 7, d <= 10
@@ -69,7 +69,7 @@ __host__ __device__ constexpr uint32_t tree_start(int32_t d) {
 struct TreeLayout {
   int32_t levels;
   uint32_t entries;
-  size_t recs, keys, total;
+  size_t boxes, vals, keys, total;
 };
 inline TreeLayout tree_layout(size_t n, size_t t) {
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
@@ -77,8 +77,9 @@ inline TreeLayout tree_layout(size_t n, size_t t) {
   l.levels = 1;
   while ((size_t(1) << (3 * l.levels)) < n) ++l.levels;
   l.entries = tree_start(l.levels) + uint32_t((n + 7) & ~size_t(7));
-  l.recs = 256;
-  l.keys = l.recs + al(size_t(l.entries) * 2 * t);
+  l.boxes = 256;
+  l.vals = l.boxes + al(size_t(tree_start(l.levels - 1)) * 16 * t);
+  l.keys = l.vals + al(((n + 7) & ~size_t(7)) * t);
   // callers size the buffer as they did for two linked nodes of 2t + 8 bytes
   // per texel and the texels and keys beside them, which always holds this
   l.total = 256 + al(2 * n * (2 * t + 8)) + al((n + 4) * t) + al((n + 4) * 4);
@@ -153,8 +154,9 @@ struct FrameArgs {
   // search formats (SB_GUIDE_U8XN / U16XN): the tree's sections, the
   // texel size and the eight channel weights (byte k = weight of element k,
   // 0 past the guide's channels)
-  const void *t_recs;
+  const void *t_boxes;
   const uint32_t *t_keys;
+  uint32_t t_vals, t_last;
   int32_t t_levels;
   int32_t texel;
   uint32_t wn[2];

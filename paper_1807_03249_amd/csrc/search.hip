@@ -184,29 +184,43 @@ struct Weights {
   }
 };
 
-// sum_k w_k d_k^2 from q to the nearest point of the box [lo, hi] (its texel
-// where lo = hi): the two saturating differences of an element are not both
-// above zero, so their union is its distance to the box.
-template <int D, int S>
-__device__ __forceinline__ typename DistOf<D>::type box_dist(const Pairs<D, S> &q, const Tx<S> &lo,
-                                                            const Tx<S> &hi,
-                                                            const Weights<D, S> &wt) {
-  const Pairs<D, S> l = to_pairs<D, S>(lo), h = to_pairs<D, S>(hi);
-  typename DistOf<D>::type acc = 0;
-  for_elems<0, kPairs<D, S>>([&](auto k) {
+// sum_k w_k d_k^2 from q to the nearest point of each of N boxes [lo, hi]
+// (their texels where lo = hi): the two saturating differences of an element
+// are not both above zero, so their union is its distance to the box.  The
+// last pair is left out where its elements carry no weight (five channels
+// fill five bytes of eight), a branch of the whole wave.
+template <int D, int S, int N>
+__device__ __forceinline__ void box_dists(const Pairs<D, S> &q, const Tx<S> *lo, const Tx<S> *hi,
+                                          const Weights<D, S> &wt,
+                                          typename DistOf<D>::type *acc) {
+  constexpr int P = kPairs<D, S>;
+  Pairs<D, S> l[N], h[N];
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    l[n] = to_pairs<D, S>(lo[n]), h[n] = to_pairs<D, S>(hi[n]);
+    acc[n] = 0;
+  }
+  auto pair = [&](auto k) {
     constexpr int K = decltype(k)::value;
-    const u16x2 d = __builtin_elementwise_sub_sat(l.p[K], q.p[K]) |
-                    __builtin_elementwise_sub_sat(q.p[K], h.p[K]);
-    if constexpr (D == 8) {
-      // d <= 255 and w <= 127: their product fits 16 bits
-      acc = __builtin_amdgcn_udot2(d, d * wt.p.p[K], acc, false);
-    } else {
-      const uint32_t d0 = d.x, d1 = d.y;
-      acc += uint64_t(__umul24(d0, weight<2 * K>(wt.w))) * d0;
-      acc += uint64_t(__umul24(d1, weight<2 * K + 1>(wt.w))) * d1;
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const u16x2 d = __builtin_elementwise_sub_sat(l[n].p[K], q.p[K]) |
+                      __builtin_elementwise_sub_sat(q.p[K], h[n].p[K]);
+      if constexpr (D == 8) {
+        // d <= 255 and w <= 127: their product fits 16 bits
+        acc[n] = __builtin_amdgcn_udot2(d, d * wt.p.p[K], acc[n], false);
+      } else {
+        const uint32_t d0 = d.x, d1 = d.y;
+        acc[n] += uint64_t(__umul24(d0, weight<2 * K>(wt.w))) * d0;
+        acc[n] += uint64_t(__umul24(d1, weight<2 * K + 1>(wt.w))) * d1;
+      }
     }
-  });
-  return acc;
+  };
+  for_elems<0, P == 4 ? 3 : P>(pair);
+  if constexpr (P == 4) {
+    const bool last = D == 8 ? __builtin_bit_cast(uint32_t, wt.p.p[3]) != 0u : wt.w[1] >> 16 != 0u;
+    if (last) pair(std::integral_constant<int, 3>());
+  }
 }
 
 // A distance in 29 bits, weakly monotone (so an order of packed values never
@@ -219,44 +233,44 @@ __device__ __forceinline__ uint32_t pack_dist(uint64_t d) {
 }
 
 struct TreeView {
-  const void *recs;
+  const void *boxes;
   const uint32_t *keys;
+  uint32_t vals;  // bytes from the boxes to the texels
+  uint32_t last;  // the last texel
   int32_t levels;
 };
 
 TreeView tree_view(const void *tree, size_t n, size_t t) {
   const TreeLayout l = tree_layout(n, t);
   const char *b = static_cast<const char *>(tree);
-  return TreeView{b + l.recs, reinterpret_cast<const uint32_t *>(b + l.keys), l.levels};
+  return TreeView{b + l.boxes, reinterpret_cast<const uint32_t *>(b + l.keys),
+                  uint32_t(l.vals - l.boxes), uint32_t(n - 1), l.levels};
 }
 
-// The records of entries i .. i + N - 1.
+// N texels from p on (dword-aligned vectors).
 template <int S, int N>
-__device__ __forceinline__ void load_recs(const void *recs, uint32_t i, Tx<S> *lo, Tx<S> *hi) {
-  constexpr int W = 2 * S / 4 * N, V = W % 4 == 0 ? 4 : 2;  // words, words per load
+__device__ __forceinline__ void load_run(const SB_GLOBAL unsigned char *p, Tx<S> *t) {
+  constexpr int W = S / 4 * N, V = W % 4 == 0 ? 4 : W;  // words, words per load
   typedef uint32_t vec __attribute__((ext_vector_type(V), aligned(4)));
-  const SB_GLOBAL vec *p = reinterpret_cast<const SB_GLOBAL vec *>(
-      glb(static_cast<const unsigned char *>(recs)) + uint64_t(i * uint32_t(2 * S)));
   vec v[W / V];
 #pragma unroll
-  for (int k = 0; k < W / V; ++k) v[k] = p[k];
+  for (int k = 0; k < W / V; ++k) v[k] = reinterpret_cast<const SB_GLOBAL vec *>(p)[k];
 #pragma unroll
-  for (int n = 0; n < N; ++n)
-#pragma unroll
-    for (int k = 0; k < S / 4; ++k) {
-      const int l = n * (S / 2) + k, h = l + S / 4;
-      lo[n].w[k] = v[l / V][l % V];
-      hi[n].w[k] = v[h / V][h % V];
-    }
+  for (int k = 0; k < W; ++k) t[k / (S / 4)].w[k % (S / 4)] = v[k / V][k % V];
 }
 
+// Entry e's box, among its siblings' in their parent's record.
 template <int S>
-__device__ __forceinline__ void store_rec(void *recs, uint32_t i, const Tx<S> &lo,
+__device__ __forceinline__ SB_GLOBAL unsigned char *box_at(void *boxes, uint32_t e) {
+  return glb(static_cast<unsigned char *>(boxes)) +
+         uint64_t(((e - 1u) >> 3) * uint32_t(16 * S) + ((e - 1u) & 7u) * uint32_t(S));
+}
+template <int S>
+__device__ __forceinline__ void store_box(void *boxes, uint32_t e, const Tx<S> &lo,
                                           const Tx<S> &hi) {
-  SB_GLOBAL uint32_t *p = reinterpret_cast<SB_GLOBAL uint32_t *>(
-      glb(static_cast<unsigned char *>(recs)) + uint64_t(i * uint32_t(2 * S)));
+  SB_GLOBAL uint32_t *p = reinterpret_cast<SB_GLOBAL uint32_t *>(box_at<S>(boxes, e));
 #pragma unroll
-  for (int k = 0; k < S / 4; ++k) p[k] = lo.w[k], p[S / 4 + k] = hi.w[k];
+  for (int k = 0; k < S / 4; ++k) p[k] = lo.w[k], p[2 * S + k] = hi.w[k];
 }
 
 // v of another lane of the row by the DPP pattern CTRL (every lane of the
@@ -286,11 +300,12 @@ __device__ __forceinline__ T group_min(T v) {
 // The exact lookup of a texel by an aligned group of G lanes, one tree node
 // per step: the source coordinate x | y << 16 of the texel nearest to q under
 // the weights, ties to the smallest raster index.  Lane g takes the node's
-// children g N .. g N + N - 1 (N = 8 / G): their records come in one round
+// children g N .. g N + N - 1 (N = 8 / G): their boxes come in one round
 // trip, the nearest child is next and the lanes keep the others' packed
-// distances in LDS, one slot per level of the path (`live`: the levels whose
-// slot may still hold a child), so nothing is kept in scratch memory and
-// there is one dependent round trip per node.
+// distances in LDS, one slot per level of the path.  The least distance left
+// on each level stays in a register (lane g: levels g N .. g N + N - 1), so
+// the deepest level worth going back to is known without looking; nothing is
+// kept in scratch memory and there is one dependent round trip per node.
 //
 // (best, best_key) may start at a real source texel's distance and
 // coordinate (a candidate the caller already measured): every subtree that
@@ -300,17 +315,18 @@ template <int D, int S, int G>
 struct Search {
   typedef typename DistOf<D>::type Dist;
   static constexpr int N = 8 / G;
-  static constexpr uint32_t kGone = 0xFFFFFFFFu;  // a slot entry without a child
+  static constexpr uint32_t kGone = 0xFFFFFFFFu;  // no child
   Pairs<D, S> q;
   Dist best;
-  uint32_t best_key, pos, live;
+  uint32_t best_key, pos, left[N];
   int32_t depth;
 
   __device__ __forceinline__ void start(const Tx<S> &t, Dist b, uint32_t k) {
     q = to_pairs<D, S>(t);
     best = b, best_key = k;
-    pos = live = 0u;
-    depth = 0;
+    pos = 0u, depth = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) left[j] = kGone;
   }
   __device__ __forceinline__ static uint32_t least(const uint32_t *pk) {
     uint32_t m = pk[0];
@@ -318,73 +334,83 @@ struct Search {
     for (int j = 1; j < N; ++j) m = min(m, pk[j]);
     return group_min<G>(m);
   }
-  // Take the nearest child m of level d's slot values pk; the rest stay.
-  __device__ __forceinline__ void descend(uint32_t m, int32_t d, uint32_t *pk, uint32_t *slots) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) pk[j] = pk[j] == m ? kGone : pk[j];
-    if (least(pk) != kGone) {
-#pragma unroll
-      for (int j = 0; j < N; ++j) slots[64 * N * d + j] = pk[j];
-      live |= 1u << d;
-    } else {
-      live &= ~(1u << d);
-    }
-    pos = 8u * (pos >> (3 * (depth - d))) + (m & 7u);
-    depth = d + 1;
+  // (d, k) before (e, f), as one comparison where both fit 64 bits
+  __device__ __forceinline__ static bool nearer(Dist d, uint32_t k, Dist e, uint32_t f) {
+    if constexpr (D == 8) return ((uint64_t(d) << 32) | k) < ((uint64_t(e) << 32) | f);
+    else return (d < e) | ((d == e) & (k < f));
   }
   // One node; true when the search is over.  `slots`: the lane's N words of
   // level 0, a level every 64 N words.
   __device__ __forceinline__ bool step(const TreeView &tv, const Weights<D, S> &wt,
                                        uint32_t *slots) {
-    const uint32_t c0 = N * (threadIdx.x & uint32_t(G - 1));
-    const uint32_t i = tree_start(depth + 1) + 8u * pos + c0;
+    const uint32_t c0 = N * (threadIdx.x & uint32_t(G - 1)), node = tree_start(depth) + pos;
+    const uint32_t first = 8u * pos + c0;  // the lane's first child on its level
+    const uint32_t last = tv.last >> (3 * (tv.levels - 1 - depth));  // that level's last entry
+    const bool leaf = depth + 1 == tv.levels;
+    // one pair of loads for either kind of children: a texel is its own box
+    const uint32_t at = leaf ? tv.vals + first * uint32_t(S) : (node * 16u + c0) * uint32_t(S);
+    const SB_GLOBAL unsigned char *base = glb(static_cast<const unsigned char *>(tv.boxes));
     Tx<S> lo[N], hi[N];
-    uint32_t key[N];
-    load_recs<S, N>(tv.recs, i, lo, hi);
-#pragma unroll
-    for (int j = 0; j < N; ++j) key[j] = glb(tv.keys)[i + uint32_t(j)];
+    load_run<S, N>(base + uint64_t(at), lo);
+    load_run<S, N>(base + uint64_t(leaf ? at : at + 8u * S), hi);
+    const SB_GLOBAL uint32_t *keys = glb(tv.keys) + uint64_t(8u * node + 1u + c0);
+    Tx<4> key[N];
+    if (leaf) load_run<4, N>(reinterpret_cast<const SB_GLOBAL unsigned char *>(keys), key);
     Dist d[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) d[j] = box_dist<D, S>(q, lo[j], hi[j], wt);
-    uint32_t pk[N];
-    if (depth + 1 == tv.levels) {  // the children are texels
+    box_dists<D, S, N>(q, lo, hi, wt, d);
+    uint32_t pk[N], m = kGone;
+    int32_t level = depth;
+    if (leaf) {
       Dist dm = ~Dist(0);
       uint32_t km = kNoTreeKey;
 #pragma unroll
-      for (int j = 0; j < N; ++j)
-        if (key[j] != kNoTreeKey && (d[j] < dm || (d[j] == dm && key[j] < km)))
-          dm = d[j], km = key[j];
+      for (int j = 0; j < N; ++j) {
+        const bool in = (first + uint32_t(j) <= last) & nearer(d[j], key[j].w[0], dm, km);
+        dm = in ? d[j] : dm, km = in ? key[j].w[0] : km;
+      }
       const Dist gd = group_min<G>(dm);
       const uint32_t gk = group_min<G>(dm == gd ? km : kNoTreeKey);
-      if (gd < best || (gd == best && gk < best_key)) best = gd, best_key = gk;
+      const bool in = nearer(gd, gk, best, best_key);
+      best = in ? gd : best, best_key = in ? gk : best_key;
     } else {
+      bool tie = false;
 #pragma unroll
       for (int j = 0; j < N; ++j) {
-        const bool in = key[j] != kNoTreeKey &&
-                        (d[j] < best || (d[j] == best && key[j] < best_key));
+        const bool in = (first + uint32_t(j) <= last) & (d[j] <= best);
         pk[j] = in ? (pack_dist(d[j]) << 3) | (c0 + uint32_t(j)) : kGone;
+        tie |= in & (d[j] == best);
       }
-      const uint32_t m = least(pk);
-      if (m != kGone) {
-        descend(m, depth, pk, slots);
-        return false;
-      }
-    }
-    // back to the deepest level with a child left that is not farther than
-    // the best so far
-    const uint32_t reach = (pack_dist(best) << 3) | 7u;
-    while (live != 0u) {
-      const int32_t l = 31 - __builtin_clz(live);
+      if (tie) {  // seldom: as far as the best, worth a visit only for a smaller key
 #pragma unroll
-      for (int j = 0; j < N; ++j) pk[j] = slots[64 * N * l + j];
-      const uint32_t m = least(pk);
-      if (m <= reach) {
-        descend(m, l, pk, slots);
-        return false;
+        for (int j = 0; j < N; ++j)
+          if (pk[j] != kGone && d[j] == best && keys[j] >= best_key) pk[j] = kGone;
       }
-      live &= ~(1u << l);
+      m = least(pk);
     }
-    return true;
+    if (m == kGone) {
+      // back to the deepest level with a child left that is not farther than
+      // the best so far
+      const uint32_t reach = (pack_dist(best) << 3) | 7u;
+      uint32_t back = 8u;  // 7 - level of the deepest
+#pragma unroll
+      for (int j = 0; j < N; ++j) back = left[j] <= reach ? 7u - c0 - uint32_t(j) : back;
+      back = group_min<G>(back);
+      if (back == 8u) return true;
+      level = int32_t(7u - back);
+#pragma unroll
+      for (int j = 0; j < N; ++j) pk[j] = slots[64 * N * level + j];
+      m = least(pk);
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) pk[j] = pk[j] == m ? kGone : pk[j];
+#pragma unroll
+    for (int j = 0; j < N; ++j) slots[64 * N * level + j] = pk[j];
+    const uint32_t rest = least(pk);
+#pragma unroll
+    for (int j = 0; j < N; ++j) left[j] = uint32_t(level) == c0 + uint32_t(j) ? rest : left[j];
+    pos = 8u * (pos >> (3 * (depth - level))) + (m & 7u);
+    depth = level + 1;
+    return false;
   }
 };
 
@@ -708,7 +734,7 @@ __global__ void __launch_bounds__(256) k_tree_split(SplitArgs a) {
 
 struct SortArgs {
   TexelsIn in;
-  void *recs;
+  void *boxes, *vals;
   uint32_t *keys;
   int32_t levels;
   uint32_t wn[2];
@@ -795,9 +821,8 @@ __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
     if (v == kNone) continue;
     const Tx<S> t = tex[v & (kSortBlock - 1u)];
     const uint32_t key = texel_key(a.in, first + (v & (kSortBlock - 1u)));
-    const uint32_t e = tree_start(a.levels) + first + 4 * tid + j;
-    store_rec<S>(a.recs, e, t, t);
-    glb(a.keys)[e] = key;
+    store_tx<S>(a.vals, first + 4 * tid + j, t);
+    glb(a.keys)[tree_start(a.levels) + first + 4 * tid + j] = key;
     const Pairs<D, S> p = to_pairs<D, S>(t);
     b.add(p, p);
     mk = min(mk, key);
@@ -806,7 +831,7 @@ __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
   auto node = [&](int32_t up, uint32_t p) {
     if (up >= a.levels || mk == kNoTreeKey) return;
     const uint32_t e = tree_start(a.levels - up) + p;
-    store_rec<S>(a.recs, e, from_pairs<D, S>(b.lo), from_pairs<D, S>(b.hi));
+    store_box<S>(a.boxes, e, from_pairs<D, S>(b.lo), from_pairs<D, S>(b.hi));
     glb(a.keys)[e] = mk;
   };
 #pragma unroll
@@ -828,7 +853,7 @@ __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
 // The levels above k_tree_sort's (one workgroup: at most 2^17 nodes' records
 // are read), and the header.
 template <int D, int S>
-__global__ void __launch_bounds__(1024) k_tree_top(void *recs, uint32_t *keys, int32_t levels,
+__global__ void __launch_bounds__(1024) k_tree_top(void *boxes, uint32_t *keys, int32_t levels,
                                                    uint32_t n, uint32_t *header,
                                                    uint32_t channels) {
   for (int32_t up = 4; up < levels; ++up) {
@@ -839,12 +864,14 @@ __global__ void __launch_bounds__(1024) k_tree_top(void *recs, uint32_t *keys, i
       b.clear();
       uint32_t mk = kNoTreeKey;
       for (uint32_t c = 8 * i; c < min(8 * i + 8, kids); ++c) {
+        const SB_GLOBAL unsigned char *p = box_at<S>(boxes, from + c);
         Tx<S> lo, hi;
-        load_recs<S, 1>(recs, from + c, &lo, &hi);
+        load_run<S, 1>(p, &lo);
+        load_run<S, 1>(p + 8 * S, &hi);
         b.add(to_pairs<D, S>(lo), to_pairs<D, S>(hi));
         mk = min(mk, glb(keys)[from + c]);
       }
-      store_rec<S>(recs, to + i, from_pairs<D, S>(b.lo), from_pairs<D, S>(b.hi));
+      store_box<S>(boxes, to + i, from_pairs<D, S>(b.lo), from_pairs<D, S>(b.hi));
       glb(keys)[to + i] = mk;
     }
     __syncthreads();
@@ -861,7 +888,7 @@ __global__ void __launch_bounds__(1024) k_tree_top(void *recs, uint32_t *keys, i
 // ------------------------------------------------------------- frame passes
 
 __device__ inline TreeView frame_tree(const FrameArgs &a) {
-  return TreeView{a.t_recs, a.t_keys, a.t_levels};
+  return TreeView{a.t_boxes, a.t_keys, a.t_vals, a.t_last, a.t_levels};
 }
 
 // Record idx of the padded seed table: the seed of its cell and the
@@ -950,73 +977,128 @@ __global__ void __launch_bounds__(256) k_assign_n(FrameArgs a) {
   }
 }
 
-// The own lookups of the pixels no level accepted (fallback chunk code): a
-// 16 x 16 tile lists them in LDS (each wave an 8 x 8 quarter: neighbours'
-// searches take similar paths) and its groups of G lanes take them in turn,
-// a group starting its next search as soon as its last one ends.  A search
-// starts from the candidate the level loop left in the vote-distance slot
-// (its distance measured again here), then the slot takes the result's vote
-// distance.
+// The own lookups of the pixels no level accepted (fallback chunk code).
+// Those pixels cluster (whole tiles fall back beside tiles where none does)
+// and searches differ in length, so work is dealt as it is taken: a wave
+// draws another 8 x 4 tile whenever its list of pixels runs short, and its
+// groups of G lanes take the list's next pixels as their searches end (once
+// two wait: a search's first load holds up the whole wave).  A search starts
+// from the candidate the level loop left in the vote-distance slot (its
+// distance measured again here, for the whole tile at once), then the slot
+// takes the result's vote distance.
+//
+// The tiles drawn are counted in the seed table, which has served its purpose
+// by now: the offset words of the finest level's empty records left of its
+// rows, which the seed pass writes as 0 and nothing reads.  One counter would
+// be too few (draws of one word follow one another at 16 ns: 32640 of them
+// made the pass take 0.8 ms), so up to 64 counters deal every 64th tile each.
+// Without levels there is no table; every pixel falls back then, and the
+// waves take every n-th tile.
+//
+// Bound by VALU issue (69 % of the chip's over the pass, 215 instructions per
+// node of a wave's 32 searches) and by the last searches.  The 414 k searches
+// of a 1080p frame with five 8-bit channels: 330 us; one search per lane in
+// the linked binary tree took 1300.  Fixed 16 x 16 tiles per workgroup 440,
+// draws of 8 x 8 370; four lanes per search instead of two 350 (for four
+// 16-bit channels 610 k searches in 245, and 320 with four lanes).
+constexpr uint32_t kFallbackQueue = 64;  // under 64 / G <= 32 waiting and a tile's 32
+
 template <int D, int S, int G>
 __global__ void __launch_bounds__(256) k_fallback_n(FrameArgs a) {
   typedef typename DistOf<D>::type Dist;
+  struct Entry {
+    uint32_t xy, key;
+    Dist dist;
+  };
   extern __shared__ uint32_t stack[];
-  __shared__ uint8_t list[256];
-  __shared__ uint32_t count;
-  const uint32_t tid = threadIdx.x;
-  const uint32_t tiles_x = (uint32_t(a.w) + 15u) / 16u;
-  const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
-  const uint32_t x0 = (tile % tiles_x) * 16u, y0 = (tile / tiles_x) * 16u;
-  // pixel t of the tile
-  auto px = [&](uint32_t t) { return x0 + ((t >> 6) & 1u) * 8u + (t & 7u); };
-  auto py = [&](uint32_t t) { return y0 + (t >> 7) * 8u + ((t >> 3) & 7u); };
-  if (tid == 0) count = 0u;
-  __syncthreads();
-  bool need = px(tid) < uint32_t(a.w) && py(tid) < uint32_t(a.h);
-  if (need)
-    need = (glb(a.out_chunk)[__umul24(py(tid), uint32_t(a.w)) + px(tid)] >> 26) ==
-           uint32_t(a.lv.count);
-  const uint64_t bal = __ballot(need);
-  uint32_t base = 0;
-  if ((tid & 63u) == 0 && bal != 0) base = atomicAdd(&count, uint32_t(__popcll(bal)));
-  base = __builtin_amdgcn_readfirstlane(base);
-  const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-      uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u));
-  if (need) list[base + below] = uint8_t(tid);
-  __syncthreads();
-  const uint32_t n = count;
-  uint32_t e = tid / G;
-  if (e >= n) return;
+  __shared__ Entry queues[4][kFallbackQueue];
+  const uint32_t lane = threadIdx.x & 63u;
+  Entry *queue = queues[threadIdx.x >> 6];
+  const uint32_t tiles_x = (uint32_t(a.w) + 7u) / 8u;
+  const uint32_t tiles = tiles_x * ((uint32_t(a.h) + 3u) / 4u);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
+  const int32_t L = a.lv.count;
+  uint32_t *drawn = nullptr;
+  uint32_t next = wave, stride = gridDim.x * 4u;
+  if (L > 0) {
+    const uint32_t rows = uint32_t(a.lv.cells_y[L - 1] + 2);
+    stride = min(min(rows, 64u), stride);  // counters, each with a wave at least
+    next = wave % stride;
+    drawn = &a.seeds[a.lv.poffset[L - 1] + int32_t(next) * (a.lv.cells_x[L - 1] + 2)].y;
+  }
+  uint32_t head = 0, fill = 0;  // the list: places head .. head + fill - 1
+  bool more = true;
   const TreeView tv = frame_tree(a);
   const Weights<D, S> wt(a.wn);
   uint32_t *slots = lane_slots<G>(tv, stack);
   Search<D, S, G> s;
-  uint32_t x, y, pidx;
-  auto begin = [&]() {
-    x = px(list[e]), y = py(list[e]);
-    pidx = __umul24(y, uint32_t(a.w)) + x;
-    const uint32_t ckey = glb(a.offsets)[pidx];
-    const Tx<S> gt = load_tx<S>(a.tgt_guide, pidx);
-    Dist cd = ~Dist(0);
-    if (ckey != 0xFFFFFFFFu) {
-      const uint32_t cidx = __umul24(ckey >> 16, uint32_t(a.sw)) + (ckey & 0xFFFFu);
-      cd = tx_dist<D, S>(gt, load_tx<S>(a.src_guide, cidx), a.wn);
-    }
-    s.start(gt, cd, ckey);
-  };
-  begin();
+  s.start(Tx<S>{}, 0, 0u);
+  uint32_t xy = 0, pidx = 0;
+  bool busy = false;
   for (;;) {
-    if (!s.step(tv, wt, slots)) continue;
-    if ((tid & uint32_t(G - 1)) == 0) {
-      const uint32_t u = s.best_key;
-      const uint32_t off =
-          pack_off(int32_t(u & 0xFFFFu) - int32_t(x), int32_t(u >> 16) - int32_t(y));
-      glb(a.offsets)[pidx] = vote_distance(a, off);
-      if (a.out_nnf) glb(a.out_nnf)[pidx] = u;
+    const uint64_t idle = __ballot(!busy);
+    const uint32_t waiting = uint32_t(__popcll(idle)) / G;
+    if (waiting >= 2u && (more || fill != 0u)) {
+      while (more && fill < waiting) {
+        uint32_t tile = next;
+        if (drawn) {
+          uint32_t t = 0;
+          if (lane == 0) t = atomicAdd(drawn, 1u);
+          tile += __builtin_amdgcn_readfirstlane(t) * stride;
+        } else {
+          next += stride;
+        }
+        more = tile < tiles;
+        const uint32_t ty = tile / tiles_x;
+        const uint32_t x = (tile - ty * tiles_x) * 8u + (lane & 7u), y = ty * 4u + (lane >> 3);
+        const uint32_t at = __umul24(y, uint32_t(a.w)) + x;
+        bool need = more && lane < 32u && x < uint32_t(a.w) && y < uint32_t(a.h);
+        uint32_t code = 0, ckey = 0;
+        Tx<S> gt = {};
+        if (need) {
+          code = glb(a.out_chunk)[at], ckey = glb(a.offsets)[at];
+          gt = load_tx<S>(a.tgt_guide, at);
+        }
+        need = need && (code >> 26) == uint32_t(L);
+        const uint64_t bal = __ballot(need);
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+            uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u));
+        if (need) {
+          Dist cd = ~Dist(0);
+          if (ckey != 0xFFFFFFFFu) {
+            const uint32_t cidx = __umul24(ckey >> 16, uint32_t(a.sw)) + (ckey & 0xFFFFu);
+            cd = tx_dist<D, S>(gt, load_tx<S>(a.src_guide, cidx), a.wn);
+          }
+          queue[(head + fill + below) % kFallbackQueue] = Entry{pack_xy(x, y), ckey, cd};
+        }
+        fill += uint32_t(__popcll(bal));
+      }
+      wave_lds_sync();
+      const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+                                uint32_t(idle >> 32),
+                                __builtin_amdgcn_mbcnt_lo(uint32_t(idle), 0u)) / G;
+      if (!busy && rank < fill) {
+        busy = true;
+        const Entry en = queue[(head + rank) % kFallbackQueue];
+        xy = en.xy;
+        pidx = __umul24(xy >> 16, uint32_t(a.w)) + (xy & 0xFFFFu);
+        s.start(load_tx<S>(a.tgt_guide, pidx), en.dist, en.key);
+      }
+      wave_lds_sync();
+      const uint32_t took = min(waiting, fill);
+      head += took, fill -= took;
     }
-    e += 256u / G;
-    if (e >= n) break;
-    begin();
+    if (__ballot(busy) == 0ull) break;  // (the waiting groups found no pixel left)
+    if (busy && s.step(tv, wt, slots)) {
+      busy = false;
+      if ((lane & uint32_t(G - 1)) == 0) {
+        const uint32_t u = s.best_key;
+        const uint32_t off = pack_off(int32_t(u & 0xFFFFu) - int32_t(xy & 0xFFFFu),
+                                      int32_t(u >> 16) - int32_t(xy >> 16));
+        glb(a.offsets)[pidx] = vote_distance(a, off);
+        if (a.out_nnf) glb(a.out_nnf)[pidx] = u;
+      }
+    }
   }
 }
 
@@ -1032,10 +1114,14 @@ __global__ void __launch_bounds__(256) k_tree_query(TreeView tv, const void *q, 
   if ((threadIdx.x & uint32_t(G - 1)) == 0) glb(out)[i] = u;
 }
 
-// Lanes per search of the fallback pass, and up to how many queries eight
-// lanes take one rather than four.
-constexpr int kFallbackLanes = 4;
+// Lanes per search of the fallback pass (measured there), and up to how many
+// queries eight lanes take one rather than four: eight give the shorter chain
+// while all searches are on the chip at once (65536 of five channels 58 us,
+// 69 with four lanes, 90 with two), four more searches per instruction beyond.
+constexpr int kFallbackLanes = 2;
 constexpr int64_t kQueryWide = 65536;
+// Workgroups of the fallback pass: what the chip holds.
+constexpr unsigned kFallbackGrid = 2048;
 
 // ------------------------------------------------------------------- host
 
@@ -1128,9 +1214,10 @@ hipError_t launch_search_frame(const FrameArgs &a, hipEvent_t *ev, hipStream_t s
       if (e != hipSuccess) return e;
     }
     k_assign_n<D, S><<<tiles, 256, 0, stream>>>(a);
-    const uint32_t ftiles = ((uint32_t(a.w) + 15u) / 16u) * ((uint32_t(a.h) + 15u) / 16u);
+    const uint32_t ftiles = ((uint32_t(a.w) + 7u) / 8u) * ((uint32_t(a.h) + 3u) / 4u);
+    const unsigned fblocks = ftiles < 4 * kFallbackGrid ? blocks_for(ftiles, 4) : kFallbackGrid;
     k_fallback_n<D, S, kFallbackLanes>
-        <<<ftiles, 256, stack_bytes<kFallbackLanes>(a.t_levels), stream>>>(a);
+        <<<fblocks, 256, stack_bytes<kFallbackLanes>(a.t_levels), stream>>>(a);
     return hipGetLastError();
   });
 }
@@ -1198,9 +1285,9 @@ int sb_tree_build(const void *guide, int32_t fmt, int32_t channels, int32_t sw, 
       in.vals = a.vals_out;
       in.keys = a.keys_out;
     }
-    const SortArgs a = {in, tb + l.recs, keys, l.levels, {wn[0], wn[1]}, channels};
+    const SortArgs a = {in, tb + l.boxes, tb + l.vals, keys, l.levels, {wn[0], wn[1]}, channels};
     k_tree_sort<D, S><<<nblk, 512, 0, stream>>>(a);
-    k_tree_top<D, S><<<1, 1024, 0, stream>>>(tb + l.recs, keys, l.levels, n,
+    k_tree_top<D, S><<<1, 1024, 0, stream>>>(tb + l.boxes, keys, l.levels, n,
                                              reinterpret_cast<uint32_t *>(tb), uint32_t(channels));
     const hipError_t ec = hipGetLastError();
     if (ec != hipSuccess) return ec;
@@ -1248,7 +1335,9 @@ namespace sb {
 void fill_tree_args(const sb_style *style, FrameArgs *a) {
   const int32_t t = search_texel_bytes(style->fmt, style->channels);
   const TreeView tv = tree_view(style->tree, size_t(style->sw) * size_t(style->sh), size_t(t));
-  a->t_recs = tv.recs;
+  a->t_boxes = tv.boxes;
+  a->t_vals = tv.vals;
+  a->t_last = tv.last;
   a->t_keys = tv.keys;
   a->t_levels = tv.levels;
   a->texel = t;

@@ -45,3 +45,43 @@ def test_16bit_table(sb, sw, sh, bits, spread):
     np.testing.assert_array_equal(st.lut.cpu().numpy().view(np.uint32), oracle.lut_build(g, bits))
     np.testing.assert_array_equal(st.label_luts.cpu().numpy().view(np.uint32),
                                   oracle.lut_build_labels(g, labels, 3, bits))
+
+
+# texel counts around a run of eight, a power of eight, one workgroup's sort
+# (2048), and the splits over the chip (an odd remainder, a last segment of one
+# texel, a full one); "few": most texels are duplicates, "one": all are,
+# "outlier": the histogram of every split has nearly all texels in one bin
+@pytest.mark.parametrize("depth,channels,sw,sh,spread,queries", [
+    (8, 5, 8, 1, "noise", 400), (8, 3, 3, 3, "noise", 400), (16, 4, 16, 4, "noise", 400),
+    (16, 7, 13, 5, "few", 400), (8, 8, 64, 32, "noise", 600), (8, 5, 683, 3, "few", 600),
+    (16, 2, 64, 64, "outlier", 600), (16, 4, 241, 17, "outlier", 600),
+    (8, 5, 128, 128, "one", 600), (8, 2, 257, 255, "few", 600), (16, 8, 300, 219, "noise", 600),
+    (8, 6, 512, 513, "smooth", 500), (8, 5, 50, 41, "smooth", 70001)])
+def test_search_tree(sb, depth, channels, sw, sh, spread, queries):
+    """The many-channel tree at every kind of size its build tells apart, and
+    queries on either side of the change from eight lanes a query to four."""
+    rng = np.random.default_rng(depth * 1000 + sw)
+    top, dt = (1 << depth) - 1, np.uint8 if depth == 8 else np.uint16
+    elems = oracle.texel_bytes(depth, channels) * 8 // depth
+    if spread == "smooth":
+        y, x = np.mgrid[0:sh, 0:sw]
+        g = np.stack([(np.sin(x / (7 + k)) + np.cos(y / (5 + k)) + 2) * top / 4
+                      for k in range(elems)], -1)
+    else:
+        g = rng.integers(0, top + 1, (sh, sw, elems))
+        if spread == "few":
+            g = g[:1, :5][np.zeros((sh, sw), int), rng.integers(0, min(sw, 5), (sh, sw))]
+        elif spread == "one":
+            g[:] = g[0, 0]
+        elif spread == "outlier":
+            g = np.where(rng.random((sh, sw, elems)) < 0.002, g, g & 7)
+    g = np.ascontiguousarray(g.astype(dt))
+    q = rng.integers(0, top + 1, (queries, elems)).astype(dt)
+    q[::3] = g.reshape(-1, elems)[rng.integers(0, sw * sh, len(q[::3]))]  # exact hits: ties
+    print(f"[gpu-case] search tree {depth}x{channels} {sw}x{sh} {spread} {queries}", flush=True)
+    import torch
+
+    st = sb.Style(np.zeros((sh, sw, 3), np.uint8), g, channels=channels)
+    qt = torch.from_numpy(q.view(np.int16) if depth == 16 else q).cuda()
+    got = st.query(qt).cpu().numpy().view(np.uint32)
+    np.testing.assert_array_equal(got, oracle.nn_query_n(g, channels, q))
