@@ -11,8 +11,10 @@
 // other channels, then over channel 1, ... -- on the grid of bin centres.
 // Keys are uint64 (distance << 32 | index), so the lexicographic minimum is
 // the integer minimum, and adding one channel's (weighted) squared distance
-// to every key of a line keeps their order.  Each pass is a brute-force minimum over
-// the 256 values of one channel, restricted to the values that hold a site.
+// to every key of a line keeps their order.  Each pass takes the minima of a
+// line over the values of one channel that hold a site; since a line's
+// minimum moves only one way from bin to bin, a few bins are searched over
+// the whole line and the others between their neighbours' minima.
 //
 // 16-bit guides (too many value tuples for a grid) bucket the source pixels
 // on a grid whose
@@ -82,84 +84,165 @@ constexpr uint64_t kNoKey = ~0ull;
 constexpr int32_t kSepTile = 16;  // columns of one pass block
 
 // f0[value tuple c0 | c1 << 8 (| c2 << 16)] = smallest raster index holding
-// it (pre-filled with ~0u); with `labels`, only pixels labelled `want`.
+// it (pre-filled with ~0u); with `labels`, only pixels labelled `want`.  Only
+// pixels that may lower an entry take an atomic: not one whose left neighbour
+// holds the same value, nor one that already finds a smaller index (a stale
+// value of a falling entry only costs an atomic): 512 x 512 normals of a
+// sphere, most of them one of few values, 3 us (8.4 with one per pixel).
 template <int FMT>
-__global__ void k_sep_sites(const void *guide, int32_t npix, uint32_t *f0, const uint8_t *labels,
-                            int32_t want) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= uint32_t(npix)) return;
-  if (labels && labels[i] != want) return;
-  const uint32_t v = FMT == SB_GUIDE_U8X2 ? uint32_t(static_cast<const uint16_t *>(guide)[i])
-                                          : static_cast<const uint32_t *>(guide)[i] & 0xFFFFFFu;
-  atomicMin(&f0[v], i);
+__global__ void __launch_bounds__(256) k_sep_sites(const void *guide, int32_t npix, uint32_t *f0,
+                                                   const uint8_t *labels, int32_t want) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  uint32_t v = ~0u;  // no value
+  if (i < uint32_t(npix) && (!labels || labels[i] == want))
+    v = FMT == SB_GUIDE_U8X2 ? uint32_t(static_cast<const uint16_t *>(guide)[i])
+                             : static_cast<const uint32_t *>(guide)[i] & 0xFFFFFFu;
+  const uint32_t left = uint32_t(__shfl_up(int(v), 1, 64));  // every lane takes part
+  if (v == ~0u || ((threadIdx.x & 63u) != 0 && v == left)) return;
+  if (f0[v] > i) atomicMin(&f0[v], i);
 }
 
 // One channel of the minimisation.  The input is [outer][256][inner]: keys,
 // or with SITES the site indices of f0 (~0u: none).  The output is
 // [outer][nb][inner] keys, or with FINAL the table entries (coordinates;
 // where no site exists at all -- a label absent from the exemplar -- the
-// entry of `fallback`).  A block takes one outer index and `ti` adjacent
-// columns: it stages the 256 x ti input keys in LDS, lists the channel
-// values that hold a key in any of its columns, and computes nb x ti
-// minima over that list.
+// entry of `fallback`).  A block takes `ti` columns, adjacent along `inner`
+// or, where that is 1, along `outer`: it stages their 256 x ti input keys in
+// LDS, lists the channel values that hold a key in any of them, and computes
+// the nb x ti minima over that list.
+//
+// For bins c < c' and values v < v', f_v(c') - f_v'(c') exceeds f_v(c) -
+// f_v'(c) (by 2 w (c' - c)(v' - v)): a value that beats a smaller one, or
+// ties with it at a smaller index, beats it for good in every later bin, so
+// the position of the minimum never falls from bin to bin.  64 / ti bins are
+// searched over the whole list, four threads each, then three between every
+// two, each only between its neighbours' positions, until every bin is done:
+// about 240 candidates per thread at 16 columns instead of 16 x 256.  VALU
+// bound (lanes wait for the longest range of their wave): the passes of a
+// 512 x 512 three-channel exemplar's 2^24 bins take 134, 133 and 165 us (138,
+// 608 and 901 with every bin searched over the whole list); a two-channel
+// one's two passes 7 and 9 us (13.4 and 13.7), there the longest thread.
+constexpr uint64_t kFarKey = 0x70000000FFFFFFFFull;  // staged for "no key": beyond every distance
+
 template <bool SITES, bool FINAL>
 __global__ __launch_bounds__(256) void k_sep_pass(const void *in, uint64_t *out, uint32_t *lut,
                                                   const uint32_t *fallback, int32_t inner,
                                                   int32_t ti, int32_t lut_bits, int32_t weight,
                                                   int32_t sw) {
   __shared__ uint64_t key[256 * kSepTile];
-  __shared__ uint8_t vlist[256];
+  __shared__ uint8_t pos[256 * kSepTile];  // list position of a bin's minimum
+  __shared__ __attribute__((aligned(4))) uint8_t vlist[256 + 4];
   __shared__ uint32_t wcount[4];
   const int32_t t = threadIdx.x;
-  const int32_t tiles = inner / ti;
-  const size_t o = blockIdx.x / uint32_t(tiles);
-  const int32_t i0 = int32_t(blockIdx.x % uint32_t(tiles)) * ti;
+  // column j of the block: its first input element, the step between its
+  // values there, and its first output element (bins are `inner` apart too)
+  const int32_t per_line = inner > 1 ? inner / ti : 1;
+  const size_t o0 = inner > 1 ? blockIdx.x / uint32_t(per_line) : size_t(blockIdx.x) * size_t(ti);
+  const int32_t i0 = inner > 1 ? int32_t(blockIdx.x % uint32_t(per_line)) * ti : 0;
+  const int32_t nb = 1 << lut_bits, sft = 8 - lut_bits;
   for (int32_t e = t; e < 256 * ti; e += 256) {
-    const int32_t v = e / ti, j = e - v * ti;
-    const size_t src = (o * 256 + size_t(v)) * size_t(inner) + size_t(i0 + j);
+    // along the fastest index of the input
+    const int32_t v = inner > 1 ? e / ti : e & 255, j = inner > 1 ? e - v * ti : e >> 8;
+    const size_t src = inner > 1 ? (o0 * 256 + size_t(v)) * size_t(inner) + size_t(i0 + j)
+                                 : (o0 + size_t(j)) * 256 + size_t(v);
     uint64_t k;
     if (SITES) {
       const uint32_t idx = static_cast<const uint32_t *>(in)[src];
-      k = idx == ~0u ? kNoKey : uint64_t(idx);
+      k = idx == ~0u ? kFarKey : uint64_t(idx);
     } else {
       k = static_cast<const uint64_t *>(in)[src];
+      k = k == kNoKey ? kFarKey : k;
     }
     key[v * kSepTile + j] = k;
   }
   __syncthreads();
   // compact list of the channel values with a key (thread t examines v = t)
   bool any = false;
-  for (int32_t j = 0; j < ti; ++j) any |= key[t * kSepTile + j] != kNoKey;
+  for (int32_t j = 0; j < ti; ++j) any |= key[t * kSepTile + j] != kFarKey;
   const uint64_t mask = __ballot(any);
   const int32_t wave = t >> 6, lane = t & 63;
   if (lane == 0) wcount[wave] = uint32_t(__popcll(mask));
   __syncthreads();
   uint32_t base = 0;
   for (int32_t w = 0; w < wave; ++w) base += wcount[w];
-  const uint32_t count = wcount[0] + wcount[1] + wcount[2] + wcount[3];
-  if (any) vlist[base + uint32_t(__popcll(mask & ((1ull << lane) - 1ull)))] = uint8_t(t);
+  const int32_t count = int32_t(wcount[0] + wcount[1] + wcount[2] + wcount[3]);
+  if (any) {
+    const int32_t at = int32_t(base) + __popcll(mask & ((1ull << lane) - 1ull));
+    vlist[at] = uint8_t(t);
+    // a whole search reads four at a time: the last value again is harmless
+    if (at == count - 1) vlist[count] = vlist[count + 1] = vlist[count + 2] = uint8_t(t);
+  }
   __syncthreads();
-  const int32_t nb = 1 << lut_bits, sft = 8 - lut_bits;
   const int32_t half = sft ? 1 << (sft - 1) : 0;
-  const int32_t j = t % ti;
-  for (int32_t b = t / ti; b < nb; b += 256 / ti) {
-    const int32_t centre = (b << sft) + half;
-    uint64_t best = kNoKey;
-    for (uint32_t n = 0; n < count; ++n) {
-      const int32_t v = vlist[n];
-      const uint64_t k = key[v * kSepTile + j];
-      const int32_t d = centre - v;
-      const uint64_t cand = k + (uint64_t(uint32_t(weight * d * d)) << 32);
-      best = (k != kNoKey && cand < best) ? cand : best;
-    }
-    const size_t dst = (o * size_t(nb) + size_t(b)) * size_t(inner) + size_t(i0 + j);
+  const int32_t j = t % ti, slot = t / ti, slots = 256 / ti;
+  uint64_t best;
+  int32_t best_at;
+  auto weigh = [&](int32_t centre, int32_t v, int32_t n, uint64_t k) {
+    const int32_t d = centre - v;
+    const uint64_t cand = k + (uint64_t(uint32_t(__mul24(weight, __mul24(d, d)))) << 32);
+    best_at = cand < best ? n : best_at;
+    best = cand < best ? cand : best;
+  };
+  auto emit = [&](int32_t b) {
+    const size_t dst = inner > 1 ? (o0 * size_t(nb) + size_t(b)) * size_t(inner) + size_t(i0 + j)
+                                 : (o0 + size_t(j)) * size_t(nb) + size_t(b);
+    const bool none = best >= kFarKey;
     if (FINAL) {
       const uint32_t idx = uint32_t(best);
-      lut[dst] = best == kNoKey ? (fallback ? fallback[dst] : 0u)
-                                : pack_xy(idx % uint32_t(sw), idx / uint32_t(sw));
+      lut[dst] = none ? (fallback ? fallback[dst] : 0u)
+                      : pack_xy(idx % uint32_t(sw), idx / uint32_t(sw));
     } else {
-      out[dst] = best;
+      out[dst] = none ? kNoKey : best;
     }
+  };
+  // the first bins, a quarter of the list per thread
+  const int32_t firsts = slots / 4, part = slot & 3;
+  int32_t step = nb > firsts ? nb / firsts : 1;
+  {
+    const int32_t b = (slot >> 2) * step, centre = (b << sft) + half;
+    best = kNoKey, best_at = 0;
+    for (int32_t n = 4 * part; n < count; n += 16) {
+      const uint32_t v4 = *reinterpret_cast<const uint32_t *>(vlist + n);
+      uint64_t k[4];
+#pragma unroll
+      for (int32_t m = 0; m < 4; ++m)
+        k[m] = key[int32_t((v4 >> (8 * m)) & 0xFFu) * kSepTile + j];
+#pragma unroll
+      for (int32_t m = 0; m < 4; ++m)
+        weigh(centre, int32_t((v4 >> (8 * m)) & 0xFFu), min(n + m, count - 1), k[m]);
+    }
+#pragma unroll
+    for (int32_t x = 1; x <= 2; x <<= 1) {
+      const uint64_t k = uint64_t(__shfl_xor((unsigned long long)best, x * ti, 64));
+      const int32_t at = __shfl_xor(best_at, x * ti, 64);
+      best_at = k < best ? at : best_at;
+      best = k < best ? k : best;
+    }
+    if (part == 0 && b < nb) {
+      emit(b);
+      pos[b * kSepTile + j] = uint8_t(best_at);
+    }
+  }
+  while (step > 1) {
+    __syncthreads();
+    const int32_t next = step >= 4 ? step / 4 : 1, per = step / next - 1;  // new bins per gap
+    for (int32_t e = slot; e < nb / step * per; e += slots) {
+      const int32_t gap = e / per, b = gap * step + (e - gap * per + 1) * next;
+      const int32_t centre = (b << sft) + half;
+      const int32_t from = pos[gap * step * kSepTile + j];
+      const int32_t to = (gap + 1) * step < nb ? int32_t(pos[(gap + 1) * step * kSepTile + j])
+                                               : count - 1;
+      best = kNoKey, best_at = from;
+      for (int32_t n = from; n <= to; n += 2) {
+        const int32_t n1 = min(n + 1, to), v0 = vlist[n], v1 = vlist[n1];
+        const uint64_t k0 = key[v0 * kSepTile + j], k1 = key[v1 * kSepTile + j];
+        weigh(centre, v0, n, k0);
+        weigh(centre, v1, n1, k1);
+      }
+      emit(b);
+      pos[b * kSepTile + j] = uint8_t(best_at);
+    }
+    step = next;
   }
 }
 
@@ -397,9 +480,10 @@ void sep_pass(const void *in, uint64_t *out, uint32_t *lut, const uint32_t *fall
   // up to kSepTile columns per block, fewer when that leaves the chip
   // short of blocks (the last pass of a two-channel table has one line of
   // 2^lut_bits columns)
-  int32_t ti = inner < kSepTile ? inner : kSepTile;
-  while (ti > 1 && outer * size_t(inner / ti) < 2048) ti >>= 1;
-  const size_t blocks = outer * size_t(inner / ti);
+  const size_t cols = outer * size_t(inner), most = inner > 1 ? size_t(inner) : outer;
+  int32_t ti = most < size_t(kSepTile) ? int32_t(most) : kSepTile;
+  while (ti > 1 && cols / size_t(ti) < 2048) ti >>= 1;
+  const size_t blocks = cols / size_t(ti);
   k_sep_pass<SITES, FINAL><<<unsigned(blocks), 256, 0, stream>>>(in, out, lut, fallback, inner,
                                                                   ti, lut_bits, weight, sw);
 }

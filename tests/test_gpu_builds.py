@@ -85,3 +85,28 @@ def test_search_tree(sb, depth, channels, sw, sh, spread, queries):
     qt = torch.from_numpy(q.view(np.int16) if depth == 16 else q).cuda()
     got = st.query(qt).cpu().numpy().view(np.uint32)
     np.testing.assert_array_equal(got, oracle.nn_query_n(g, channels, q))
+
+
+# bits around the first bins' spacing (1 to 64 bins apart), one site, one value
+# along a channel, lines without any, dense noise, and zero and large weights
+@pytest.mark.parametrize("channels,bits,spread,weights", [
+    (2, 1, "noise", None), (2, 4, "line", None), (2, 7, "sphere", None), (2, 8, "one", None),
+    (2, 8, "noise", None), (3, 1, "noise", None), (3, 2, "one", [127, 1, 3]),
+    (3, 4, "sphere", [1, 0, 127]), (3, 5, "line", [2, 3, 5]), (3, 6, "noise", None)])
+def test_8bit_table(sb, channels, bits, spread, weights):
+    """The separable passes: every bin's minimum found between its neighbours'."""
+    rng = np.random.default_rng(channels * 100 + bits)
+    sh, sw = 67, 61
+    g = rng.integers(0, 256, (sh, sw, 4 if channels == 3 else 2)).astype(np.uint8)
+    if spread == "one":
+        g[:] = g[0, 0]
+    elif spread == "line":  # one channel constant: whole planes hold no site
+        g[..., channels - 1] = 77
+    elif spread == "sphere":
+        y, x = np.mgrid[0:sh, 0:sw]
+        g[..., 0], g[..., 1] = np.clip(x * 4, 20, 200), np.clip(y * 4, 20, 200)
+    rgb = np.zeros((sh, sw, 3), np.uint8)
+    print(f"[gpu-case] 8-bit table channels={channels} bits={bits} {spread} {weights}", flush=True)
+    st = sb.Style(rgb, g, bits, weights=weights)
+    want = oracle.lut_build(g, bits, weights) if channels == 3 else oracle.lut_build(g, bits)
+    np.testing.assert_array_equal(st.lut.cpu().numpy().view(np.uint32), want)
