@@ -42,6 +42,8 @@ namespace {
 
 // Texels one workgroup sorts in LDS.
 constexpr uint32_t kSortLog = 11, kSortBlock = 1u << kSortLog;
+// Texels per workgroup of the splits before that.
+constexpr uint32_t kSplitLog = 10, kSplitBlock = 1u << kSplitLog, kSplitThreads = 256;
 // Bins of a split's histogram.
 constexpr uint32_t kBinsLog = 10, kBins = 1u << kBinsLog;
 
@@ -285,6 +287,18 @@ __device__ __forceinline__ uint64_t dpp_from(uint64_t v) {
   return lo | (hi << 32);
 }
 
+// v of lane ^ M.
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if constexpr (M == 1) return dpp_from<0xB1>(v);
+  else if constexpr (M == 2) return dpp_from<0x4E>(v);
+  else if constexpr (M == 3) return dpp_from<0x1B>(v);
+  else if constexpr (M == 7) return dpp_from<0x141>(v);   // mirrored halves of a row
+  else if constexpr (M == 8) return dpp_from<0x128>(v);   // a row rotated by eight
+  else if constexpr (M == 15) return dpp_from<0x140>(v);  // a mirrored row
+  else return uint32_t(__shfl_xor(int(v), M, 64));
+}
+
 // The least of v over each aligned group of G lanes, in every lane of the
 // group (all active): lane ^ 1, lane ^ 2, then the group's two quads (lane
 // 7 - i of the group).
@@ -510,15 +524,25 @@ struct Box {
       hi.p[k] = __builtin_elementwise_max(hi.p[k], h.p[k]);
     }
   }
-  // joined with the box of lane ^ o
-  __device__ __forceinline__ void join(int32_t o) {
+  // joined with the box of lane ^ M
+  template <int M>
+  __device__ __forceinline__ void join() {
     Pairs<D, S> l, h;
 #pragma unroll
     for (int k = 0; k < kPairs<D, S>; ++k) {
-      l.p[k] = __builtin_bit_cast(u16x2, __shfl_xor(__builtin_bit_cast(int, lo.p[k]), o, 64));
-      h.p[k] = __builtin_bit_cast(u16x2, __shfl_xor(__builtin_bit_cast(int, hi.p[k]), o, 64));
+      l.p[k] = __builtin_bit_cast(u16x2, lane_xor<M>(__builtin_bit_cast(uint32_t, lo.p[k])));
+      h.p[k] = __builtin_bit_cast(u16x2, lane_xor<M>(__builtin_bit_cast(uint32_t, hi.p[k])));
     }
     add(l, h);
+  }
+  // joined over aligned groups of n lanes (a power of two)
+  __device__ __forceinline__ void join_lanes(uint32_t n) {
+    if (n > 1) join<1>();
+    if (n > 2) join<2>();
+    if (n > 4) join<7>();
+    if (n > 8) join<15>();
+    if (n > 16) join<16>();
+    if (n > 32) join<32>();
   }
   __device__ __forceinline__ void elems(uint32_t *l, uint32_t *h) const {
     const Tx<S> tl = from_pairs<D, S>(lo), th = from_pairs<D, S>(hi);
@@ -562,21 +586,20 @@ __global__ void __launch_bounds__(256) k_tree_box(const void *guide, uint32_t n,
     const Pairs<D, S> p = to_pairs<D, S>(load_tx<S>(guide, i));
     b.add(p, p);
   }
-#pragma unroll
-  for (int32_t o = 1; o < 64; o <<= 1) b.join(o);
+  b.join_lanes(64);
   if ((tid & 63u) == 0) b.widen(words);
   __syncthreads();
   if (tid < kBoxWords<D, S>) atomicMin(box + tid, words[tid]);
 }
 
-// A level's segment of a workgroup (kSortBlock texels, so one segment) and
+// A level's segment of a workgroup (kSplitBlock texels, so one segment) and
 // how it is split.
 template <int D, int S>
 struct Segment {
   uint32_t id, first, count, half, lo;
   int32_t axis, shift;
   __device__ __forceinline__ explicit Segment(const SplitArgs &a) {
-    const uint32_t seg = blockIdx.x >> (a.lg - int32_t(kSortLog));
+    const uint32_t seg = blockIdx.x >> (a.lg - int32_t(kSplitLog));
     id = (1u << a.level) - 1u + seg;
     first = seg << a.lg;
     count = min(a.in.n - first, 1u << a.lg);
@@ -600,30 +623,30 @@ struct Segment {
   }
 };
 
-constexpr uint32_t kSplitPer = kSortBlock / 256;
+constexpr uint32_t kSplitPer = kSplitBlock / kSplitThreads;
 
 // First half of a level's splits: the histogram of every segment's texels
 // along its axis.
 template <int D, int S>
-__global__ void __launch_bounds__(256) k_tree_hist(SplitArgs a) {
+__global__ void __launch_bounds__(kSplitThreads) k_tree_hist(SplitArgs a) {
   __shared__ uint32_t bins[kBins];
   const Segment<D, S> sg(a);
   if (sg.count <= sg.half) return;  // all of it goes left
   const uint32_t tid = threadIdx.x;
 #pragma unroll
-  for (uint32_t k = 0; k < kBins; k += 256) bins[k + tid] = 0u;
+  for (uint32_t k = 0; k < kBins; k += kSplitThreads) bins[k + tid] = 0u;
   __syncthreads();
-  const uint32_t i0 = blockIdx.x * kSortBlock + tid;
+  const uint32_t i0 = blockIdx.x * kSplitBlock + tid;
   Tx<S> t[kSplitPer];
 #pragma unroll
   for (uint32_t k = 0; k < kSplitPer; ++k)
-    t[k] = load_tx<S>(a.in.vals, min(i0 + 256 * k, a.in.n - 1));
+    t[k] = load_tx<S>(a.in.vals, min(i0 + kSplitThreads * k, a.in.n - 1));
 #pragma unroll
   for (uint32_t k = 0; k < kSplitPer; ++k)
-    if (i0 + 256 * k < a.in.n) atomicAdd(&bins[sg.bin(t[k])], 1u);
+    if (i0 + kSplitThreads * k < a.in.n) atomicAdd(&bins[sg.bin(t[k])], 1u);
   __syncthreads();
 #pragma unroll
-  for (uint32_t k = 0; k < kBins; k += 256)
+  for (uint32_t k = 0; k < kBins; k += kSplitThreads)
     if (bins[k + tid] != 0u) atomicAdd(a.hist + size_t(sg.id) * kBins + k + tid, bins[k + tid]);
 }
 
@@ -635,18 +658,28 @@ __global__ void __launch_bounds__(256) k_tree_hist(SplitArgs a) {
 // guide up to the order of a bin's texels; a search's result does not depend
 // on it).  On the way the children's boxes are taken.
 template <int D, int S>
-__global__ void __launch_bounds__(256) k_tree_split(SplitArgs a) {
-  __shared__ uint32_t part[4], found[3], wave_n[4][3], base[3];
+__global__ void __launch_bounds__(kSplitThreads) k_tree_split(SplitArgs a) {
+  constexpr uint32_t W = kSplitThreads / 64;
+  __shared__ uint32_t part[W], found[3], wave_n[W][3], base[3];
   __shared__ uint32_t box[2 * kBoxWords<D, S>];
   const Segment<D, S> sg(a);
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   if (tid < 2 * kBoxWords<D, S>) box[tid] = 0xFFFFFFFFu;
+  const uint32_t i0 = blockIdx.x * kSplitBlock + tid;
+  Tx<S> t[kSplitPer];
+  uint32_t key[kSplitPer];
+#pragma unroll
+  for (uint32_t k = 0; k < kSplitPer; ++k) {
+    const uint32_t i = min(i0 + kSplitThreads * k, a.in.n - 1);
+    t[k] = load_tx<S>(a.in.vals, i);
+    key[k] = texel_key(a.in, i);
+  }
   uint32_t mid = kBins, below = sg.count, same = 0u;  // all left
   if (sg.count > sg.half) {
     const SB_GLOBAL uint32_t *hist = glb(a.hist) + size_t(sg.id) * kBins;
-    uint32_t h[kBins / 256], sum = 0;
+    uint32_t h[kBins / kSplitThreads], sum = 0;
 #pragma unroll
-    for (uint32_t k = 0; k < kBins / 256; ++k) sum += h[k] = hist[(kBins / 256) * tid + k];
+    for (uint32_t k = 0; k < kBins / kSplitThreads; ++k) sum += h[k] = hist[(kBins / kSplitThreads) * tid + k];
     uint32_t incl = sum;
 #pragma unroll
     for (uint32_t o = 1; o < 64; o <<= 1) {
@@ -658,30 +691,22 @@ __global__ void __launch_bounds__(256) k_tree_split(SplitArgs a) {
     uint32_t run = incl - sum;
     for (uint32_t w = 0; w < wave; ++w) run += part[w];
 #pragma unroll
-    for (uint32_t k = 0; k < kBins / 256; ++k) {
+    for (uint32_t k = 0; k < kBins / kSplitThreads; ++k) {
       if (run <= sg.half && sg.half < run + h[k])
-        found[0] = (kBins / 256) * tid + k, found[1] = run, found[2] = h[k];
+        found[0] = (kBins / kSplitThreads) * tid + k, found[1] = run, found[2] = h[k];
       run += h[k];
     }
     __syncthreads();
     mid = found[0], below = found[1], same = found[2];
   }
   const uint32_t take = sg.half - min(below, sg.half);  // of the median's bin, to the left
-  const uint32_t i0 = blockIdx.x * kSortBlock + tid;
-  Tx<S> t[kSplitPer];
-  uint32_t key[kSplitPer], rank[kSplitPer], cls[kSplitPer], n[3] = {0u, 0u, 0u};
-#pragma unroll
-  for (uint32_t k = 0; k < kSplitPer; ++k) {
-    const uint32_t i = min(i0 + 256 * k, a.in.n - 1);
-    t[k] = load_tx<S>(a.in.vals, i);
-    key[k] = texel_key(a.in, i);
-  }
+  uint32_t rank[kSplitPer], cls[kSplitPer], n[3] = {0u, 0u, 0u};
   const uint64_t under = (1ull << lane) - 1ull;
 #pragma unroll
   for (uint32_t k = 0; k < kSplitPer; ++k) {
     const uint32_t b = sg.bin(t[k]);
     // 0 below the median's bin, 1 in it, 2 above, 3 no texel
-    cls[k] = i0 + 256 * k >= a.in.n ? 3u : b < mid ? 0u : b == mid ? 1u : 2u;
+    cls[k] = i0 + kSplitThreads * k >= a.in.n ? 3u : b < mid ? 0u : b == mid ? 1u : 2u;
     rank[k] = 0u;
 #pragma unroll
     for (uint32_t c = 0; c < 3; ++c) {
@@ -692,9 +717,11 @@ __global__ void __launch_bounds__(256) k_tree_split(SplitArgs a) {
   }
   if (lane < 3) wave_n[wave][lane] = lane == 0 ? n[0] : lane == 1 ? n[1] : n[2];
   __syncthreads();
-  if (tid < 3)
-    base[tid] = atomicAdd(a.ctr + size_t(sg.id) * 4 + tid,
-                          wave_n[0][tid] + wave_n[1][tid] + wave_n[2][tid] + wave_n[3][tid]);
+  if (tid < 3) {
+    uint32_t sum = 0;
+    for (uint32_t w = 0; w < W; ++w) sum += wave_n[w][tid];
+    base[tid] = atomicAdd(a.ctr + size_t(sg.id) * 4 + tid, sum);
+  }
   __syncthreads();
   uint32_t at[3];
 #pragma unroll
@@ -720,8 +747,8 @@ __global__ void __launch_bounds__(256) k_tree_split(SplitArgs a) {
     else right.add(p, p);
   }
   if (a.last) return;
-#pragma unroll
-  for (int32_t o = 1; o < 64; o <<= 1) left.join(o), right.join(o);
+  left.join_lanes(64);
+  right.join_lanes(64);
   if (lane == 0) {
     left.widen(box);
     right.widen(box + kBoxWords<D, S>);
@@ -741,12 +768,79 @@ struct SortArgs {
   int32_t channels;
 };
 
-// The last kSortLog - 3 splits of kSortBlock texels, in LDS: at every size
-// 2^lg the block's segments take their boxes and axes and are sorted along
-// them (bitonic, on value << kSortLog | texel), which leaves each segment's
-// halves split at the median; then the texels' entries and those of the
-// three levels above them are written.  A wave's threads own 256 places,
-// so a sort's exchanges within 256 places need no barrier.
+// Bitonic sorting of kSortBlock keys in ascending segments of 2^lg, thread t
+// holding places 4 t .. 4 t + 3: places up to three apart are exchanged in
+// registers, within a wave's 256 by lane moves, beyond that through `ky`.
+struct Sorter {
+  uint32_t v[4];
+  __device__ __forceinline__ static void order(uint32_t &a, uint32_t &b) {
+    const uint32_t x = min(a, b);
+    b = max(a, b), a = x;
+  }
+  __device__ __forceinline__ void near() {  // places 2, then 1 apart
+    order(v[0], v[2]), order(v[1], v[3]);
+    order(v[0], v[1]), order(v[2], v[3]);
+  }
+  // keep the lesser (upper: the greater) of each place and its partner's
+  __device__ __forceinline__ void keep(const uint32_t *o, bool upper) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = upper ? max(v[r], o[r]) : min(v[r], o[r]);
+  }
+  // places J, J / 2 .. 1 apart (J <= 128)
+  template <int J>
+  __device__ __forceinline__ void merge() {
+    if constexpr (J >= 4) {
+      uint32_t o[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[r] = lane_xor<J / 4>(v[r]);
+      keep(o, (threadIdx.x & (J / 4)) != 0);
+      merge<J / 2>();
+    } else {
+      near();
+    }
+  }
+  // runs of K / 2 into runs of K, up to a wave's 256 places
+  template <int K>
+  __device__ __forceinline__ void stage(uint32_t size) {
+    if constexpr (K <= 256) {
+      if (K > size) return;
+      uint32_t o[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[r] = lane_xor<K / 4 - 1>(v[3 - r]);
+      keep(o, (threadIdx.x & (K / 8)) != 0);
+      merge<K / 4>();
+      stage<2 * K>(size);
+    }
+  }
+  __device__ __forceinline__ void far(uint32_t partner, bool flip, bool upper, uint32_t *ky) {
+    __syncthreads();
+    u32x4 *k4 = reinterpret_cast<u32x4 *>(ky);
+    k4[threadIdx.x] = u32x4{v[0], v[1], v[2], v[3]};
+    __syncthreads();
+    const u32x4 q = k4[partner];
+    const uint32_t o[4] = {flip ? q.w : q.x, flip ? q.z : q.y, flip ? q.y : q.z, flip ? q.x : q.w};
+    keep(o, upper);
+  }
+  __device__ __forceinline__ void sort(uint32_t size, uint32_t *ky) {
+    const uint32_t t = threadIdx.x;
+    order(v[0], v[1]), order(v[2], v[3]);
+    order(v[0], v[3]), order(v[1], v[2]);
+    order(v[0], v[1]), order(v[2], v[3]);
+    stage<8>(size);
+    for (uint32_t k = 512; k <= size; k <<= 1) {
+      far(t ^ (k / 4 - 1u), true, (t & (k / 8)) != 0, ky);
+      for (uint32_t j = k / 4; j >= 256; j >>= 1) far(t ^ (j / 4), false, (t & (j / 4)) != 0, ky);
+      merge<128>();
+    }
+  }
+};
+
+// The last kSortLog - 3 splits of kSortBlock texels: at every size 2^lg the
+// block's segments take their boxes and axes and are sorted along them (on
+// value << kSortLog | texel), which leaves each segment's halves split at the
+// median; then the texels' entries and those of the three levels above them
+// are written.  Bound by the chain of exchanges (276 of them, 128 blocks for a
+// 512 x 512 style): 30 us; 70 with every exchange through LDS.
 template <int D, int S>
 __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
   __shared__ Tx<S> tex[kSortBlock];
@@ -760,23 +854,23 @@ __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
   for (uint32_t k = 0; k < kSortBlock; k += 512) {
     const uint32_t i = k + tid;
     if (i < count) tex[i] = load_tx<S>(a.in.vals, first + i);
-    ky[i] = i < count ? i : kNone;
   }
   __syncthreads();
+  Sorter st;
+#pragma unroll
+  for (uint32_t j = 0; j < 4; ++j) st.v[j] = 4 * tid + j < count ? 4 * tid + j : kNone;
   for (uint32_t lg = kSortLog; lg >= 4; --lg) {
-    uint32_t own[4];
     Box<D, S> b;
     b.clear();
 #pragma unroll
     for (uint32_t j = 0; j < 4; ++j) {
-      own[j] = ky[4 * tid + j];
-      if (own[j] != kNone) {
-        own[j] &= kSortBlock - 1u;
-        const Pairs<D, S> p = to_pairs<D, S>(tex[own[j]]);
+      if (st.v[j] != kNone) {
+        st.v[j] &= kSortBlock - 1u;
+        const Pairs<D, S> p = to_pairs<D, S>(tex[st.v[j]]);
         b.add(p, p);
       }
     }
-    for (int32_t o = 1; o < 64 && uint32_t(4 * o) < (1u << lg); o <<= 1) b.join(o);
+    b.join_lanes(min(1u << (lg - 2), 64u));
     if (lg > 8) {  // the segment's waves
       if (lane == 0) wbox[wave] = b;
       __syncthreads();
@@ -788,36 +882,15 @@ __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
     const int32_t axis = split_axis<D, S>(l, h, a.wn, a.channels);
 #pragma unroll
     for (uint32_t j = 0; j < 4; ++j)
-      if (own[j] != kNone)
-        ky[4 * tid + j] = (elem_at<D, S>(tex[own[j]], axis) << kSortLog) | own[j];
-    // pairs 128 wave + lane and + 64: places of the wave's own 256 while a
-    // pair block holds at most 128 pairs
-    bool wide = false;
-    auto exchange = [&](uint32_t half, uint32_t flip) {
-      const bool w = half > 128u;
-      if (w || wide) __syncthreads();
-      else wave_lds_sync();
-      wide = w;
-#pragma unroll
-      for (uint32_t u = 0; u < 128; u += 64) {
-        const uint32_t p = 128u * wave + u + lane;
-        const uint32_t i = ((p & ~(half - 1u)) << 1) | (p & (half - 1u)), o = i ^ flip;
-        const uint32_t x = ky[i], y = ky[o];
-        ky[i] = min(x, y), ky[o] = max(x, y);
-      }
-    };
-    for (uint32_t k = 2; k <= (1u << lg); k <<= 1) {
-      exchange(k >> 1, k - 1u);
-      for (uint32_t j = k >> 2; j > 0; j >>= 1) exchange(j, j);
-    }
-    wave_lds_sync();
+      if (st.v[j] != kNone) st.v[j] |= elem_at<D, S>(tex[st.v[j]], axis) << kSortLog;
+    st.sort(1u << lg, ky);
   }
   Box<D, S> b;
   b.clear();
   uint32_t mk = kNoTreeKey;
 #pragma unroll
   for (uint32_t j = 0; j < 4; ++j) {
-    const uint32_t v = ky[4 * tid + j];
+    const uint32_t v = st.v[j];
     if (v == kNone) continue;
     const Tx<S> t = tex[v & (kSortBlock - 1u)];
     const uint32_t key = texel_key(a.in, first + (v & (kSortBlock - 1u)));
@@ -834,13 +907,15 @@ __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
     store_box<S>(a.boxes, e, from_pairs<D, S>(b.lo), from_pairs<D, S>(b.hi));
     glb(a.keys)[e] = mk;
   };
-#pragma unroll
-  for (int32_t o = 1; o < 64; o <<= 1) {
-    b.join(o);
-    mk = min(mk, uint32_t(__shfl_xor(int(mk), o, 64)));
-    if (o == 1 && (lane & 1u) == 0) node(1, (first + 4 * tid) >> 3);
-    if (o == 8 && (lane & 15u) == 0) node(2, (first + 4 * tid) >> 6);
-  }
+  b.template join<1>();
+  mk = min(mk, lane_xor<1>(mk));
+  if ((lane & 1u) == 0) node(1, (first + 4 * tid) >> 3);
+  b.template join<2>(), mk = min(mk, lane_xor<2>(mk));
+  b.template join<7>(), mk = min(mk, lane_xor<7>(mk));
+  b.template join<15>(), mk = min(mk, lane_xor<15>(mk));
+  if ((lane & 15u) == 0) node(2, (first + 4 * tid) >> 6);
+  b.template join<16>(), mk = min(mk, lane_xor<16>(mk));
+  b.template join<32>(), mk = min(mk, lane_xor<32>(mk));
   if (lane == 0) wbox[wave] = b, wkey[wave] = mk;
   __syncthreads();
   if (lane == 0 && (wave & 1u) == 0) {
@@ -1280,8 +1355,8 @@ int sb_tree_build(const void *guide, int32_t fmt, int32_t channels, int32_t sw, 
       a.wn[0] = wn[0];
       a.wn[1] = wn[1];
       a.channels = channels;
-      k_tree_hist<D, S><<<nblk, 256, 0, stream>>>(a);
-      k_tree_split<D, S><<<nblk, 256, 0, stream>>>(a);
+      k_tree_hist<D, S><<<blocks_for(n, kSplitBlock), kSplitThreads, 0, stream>>>(a);
+      k_tree_split<D, S><<<blocks_for(n, kSplitBlock), kSplitThreads, 0, stream>>>(a);
       in.vals = a.vals_out;
       in.keys = a.keys_out;
     }
