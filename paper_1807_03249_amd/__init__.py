@@ -169,16 +169,28 @@ def _check(rc: int, where: str):
         raise StyleBlitError(rc, where, detail)
 
 
-def _torch():
-    import torch
+_device_torch = None
 
-    if not torch.cuda.is_available():
-        raise RuntimeError("StyleBlit needs a HIP device; none is visible")
-    return torch
+
+def _torch():
+    """torch, once a HIP device has been found and initialised."""
+    global _device_torch
+    if _device_torch is None:
+        import torch
+
+        if not torch.cuda.is_available():
+            raise RuntimeError("StyleBlit needs a HIP device; none is visible")
+        torch.cuda.init()
+        _device_torch = torch
+    return _device_torch
 
 
 def _stream(torch) -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """Handle of torch's current stream on the current device.  Small frames
+    wait for the host, so without a Stream object: 0.2 us instead of 2.8 for
+    torch.cuda.current_stream().cuda_stream (an animation step of 853 x 481,
+    three calls, took 41 us with it and 35 without)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(torch, a, dtype=None):
@@ -519,7 +531,7 @@ class FramePlan:
         self._torch = torch
 
     def launch(self, stream=None):
-        s = self._torch.cuda.current_stream().cuda_stream if stream is None else stream
+        s = _stream(self._torch) if stream is None else stream
         rc = self._fn(*self._args, s)
         if rc != SB_OK:
             _check(rc, "sb_stylize_ex")
