@@ -145,12 +145,42 @@ bool resolve_weights(int32_t fmt, const uint8_t *in, int32_t out[3]) {
   return fmt == SB_GUIDE_U8X3 || (out[0] == 1 && out[1] == 1 && out[2] == 1);
 }
 
-bool resolve_tune(const sb_tune *in, Tune *out) {
-  out->ppt = 4;
-  out->rows = 16;
-  out->group = 2;
-  out->apx = 2;
-  out->split = 2;
+// Small frames leave the chip (1024 SIMDs) short of waves, so they take fewer
+// pixels per thread although that costs more instructions: at 256 x 256 a
+// normal-guided frame of radius 2 takes 9.0 us with 2 and 1 pixels per thread
+// (vote, level loop), 9.8 with 4 and 1 and 12.3 with the 64 x 16 voting tiles
+// and 2; at 400 x 300 and radius 3 11.8, 12.9 and 15.0.  The vote's line lies
+// where 32 x 8 tiles give every SIMD two waves: 640 x 400 takes 14.8 and 14.3
+// us at radius 3 (23.8 and 24.7 at radius 6), 640 x 480 17.8 and 15.4.  The
+// level loop's: 900 x 600 takes 21.4 us with 1 and 21.6 with 2, 1280 x 720
+// 29.4 and 28.7.  Tiles of 8 rows cost halo but fit the chip more evenly
+// (1080p 43.4 us, 46.3 with 16 rows).
+//
+// Copying uniform windows pays for its flags where most windows are uniform:
+// chunks are large when the threshold admits a step of two texels of a 16-bit
+// coordinate guide (4K with a 2048 x 2048 exemplar: t = 4096 102 us, voting in
+// place 107; 16384 89 and 102; 1024, one texel, 125 and 120) or an eighth of
+// the range of 8-bit channels (4K normals: t = 1024 98.9 and 101.1, 256 113
+// and 108; three channels 8192 95 and 102, 2048 121 and 116), and it pays on
+// large frames only (1080p at t = 4096 38.7 and 38.6, at 1024 and 512 x 512
+// texture coordinates 49 and 45).  It has less to gain from small tiles.
+Tune frame_tune(const FrameArgs &a) {
+  const int64_t px = int64_t(a.w) * a.h;
+  const uint64_t side = uint64_t(a.sw > a.sh ? a.sw : a.sh);
+  const bool tolerant = a.fmt == SB_GUIDE_U16X2   ? a.threshold * side * side >= uint64_t(1) << 34
+                        : a.fmt == SB_GUIDE_U8X2 ? a.threshold >= 1024
+                        : a.fmt == SB_GUIDE_U8X3 ? a.threshold >= 4096
+                                                 : false;
+  if (tolerant && px >= 3 << 20) return Tune{4, 16, 2, 2, 2};
+  return Tune{px <= 1 << 18 ? 2 : 4, 8, 2, px <= 1 << 19 ? 1 : 2, 1};
+}
+
+// A batch fills the chip: large tiles for the least halo (64 frames of 0.3 to
+// 2 Mpixel 1060 us, with 8 rows 1091, with uniform windows copied 1101).
+Tune batch_tune() { return Tune{4, 16, 2, 2, 1}; }
+
+bool resolve_tune(const sb_tune *in, const Tune &base, Tune *out) {
+  *out = base;
   if (!in) return true;
   if (in->blend_ppt != 0) {
     if (in->blend_ppt != 2 && in->blend_ppt != 4) return false;
@@ -301,7 +331,7 @@ int stylize_impl(const sb_style *style, const void *tgt_guide, int32_t w, int32_
                   tgt_labels))
     return SB_EINVAL;
   Tune t;
-  if (!resolve_tune(tune, &t)) return SB_EINVAL;
+  if (!resolve_tune(tune, frame_tune(a), &t)) return SB_EINVAL;
   if (!workspace) return SB_EINVAL;
   if (workspace_bytes < sb_workspace_bytes(w, h, params)) return SB_ENOMEM;
   carve_workspace(&a, workspace);

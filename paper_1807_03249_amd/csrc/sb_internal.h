@@ -97,9 +97,14 @@ constexpr int32_t kBlendMaxTW = 64, kBlendMaxTH = 16;
 struct Tune {
   int32_t ppt, rows, group, apx, split;
 };
-// Fill a Tune from the caller's sb_tune (NULL or 0 fields = defaults); false
+// The default choice for a single frame (its sizes, format and threshold) and
+// for the frames of a batch.
+struct FrameArgs;
+Tune frame_tune(const FrameArgs &a);
+Tune batch_tune();
+// Fill a Tune from the caller's sb_tune (NULL or 0 fields = base's); false
 // if a field holds an unsupported value.
-bool resolve_tune(const sb_tune *in, Tune *out);
+bool resolve_tune(const sb_tune *in, const Tune &base, Tune *out);
 
 // Padded exemplar: texels of Sw x Sh sit in rows of sw + 2 * kExMargin
 // texels with kExMargin empty (zero) texels on every side, followed by zero

@@ -127,7 +127,7 @@ int sb_serve_run(const sb_serve_config *cfg, const sb_request *reqs, int32_t n,
   if (!plain && (!cfg->desc_dev || !cfg->desc_host || !cfg->workspace)) return SB_EINVAL;
   if (!cfg->workspace) return SB_EINVAL;
   Tune tune;
-  if (!resolve_tune(&cfg->tune, &tune)) return SB_EINVAL;
+  if (!resolve_tune(&cfg->tune, batch_tune(), &tune)) return SB_EINVAL;
   if (cfg->blocks_per_cu < 0 || cfg->blocks_per_cu > 16) return SB_EINVAL;
   for (int32_t i = 0; i < n; ++i) {
     const sb_request &r = reqs[i];
