@@ -1256,8 +1256,8 @@ BuildWs build_ws(char *base, size_t n, size_t t, size_t box_words) {
   w.box_words = uint32_t(segs * box_words);
   w.hist_words = uint32_t(segs * (kBins + 4));
   w.boxes = reinterpret_cast<uint32_t *>(seg);
-  w.hist = w.boxes + w.box_words;
-  w.ctr = w.hist + segs * kBins;
+  w.hist = seg ? w.boxes + w.box_words : nullptr;
+  w.ctr = seg ? w.hist + segs * kBins : nullptr;
   return w;
 }
 
