@@ -9,6 +9,7 @@
 namespace sb {
 
 typedef short short2_t __attribute__((ext_vector_type(2)));
+typedef uint16_t ushort2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // Seed records as plain vectors in global memory.

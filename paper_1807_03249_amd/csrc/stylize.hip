@@ -40,7 +40,7 @@ __device__ inline uint32_t guide_raw(const void *g, uint32_t i) {
 }
 template <int FMT>
 __device__ inline uint32_t guide_unpack(uint32_t v) {
-  if (FMT == SB_GUIDE_U8X2) return (v & 0xFFu) | ((v >> 8) << 16);
+  if (FMT == SB_GUIDE_U8X2) return __builtin_amdgcn_perm(0u, v, 0x0C010C00u);  // bytes 0, 1
   if (FMT == SB_GUIDE_U8X3) return v & 0xFFFFFFu;
   return v;
 }
@@ -180,19 +180,23 @@ __host__ __device__ constexpr int32_t wave_recs_words(int32_t b) {
 // over each level's nine staged records, then all N * B source-guide gathers
 // in flight together, then the tests in level order.  Straight-line code
 // (levels past L rescan level L-1 and are never taken), so the gathers issue
-// back to back.
+// back to back.  Bound by VALU issue, so coordinates stay in packed pairs: the
+// source texel p + o is one packed add, its test against the exemplar's last
+// texel (`last`, a u16 pair) a packed minimum and a compare, its index a dot
+// product with (1, sw); an accepted level leaves its record's position word
+// and number, from which the chunk code is made once at the end.
 template <int FMT, int N, int B, bool SEG>
 __device__ __forceinline__ void level_group(const FrameArgs &a, const uint32_t *lpos,
-                                            const uint32_t *loff, int32_t i0, const int32_t *x,
-                                            const int32_t *y, const short2_t *p4,
+                                            const uint32_t *loff, int32_t i0, const short2_t *p4,
                                             const uint32_t *gt, const uint32_t *lt,
-                                            uint32_t *chunk, uint32_t *off, bool *done) {
+                                            uint32_t last, uint32_t row, uint32_t *seed,
+                                            uint32_t *level, uint32_t *off, bool *done) {
   const int32_t L = a.lv.count;
-  const uint32_t sw = uint32_t(a.sw), sh = uint32_t(a.sh);
   uint32_t g[B][N], wq[B][N], wo[B][N];
   bool ok[B][N];
 #pragma unroll
   for (int32_t b = 0; b < B; ++b) {
+    const ushort2_t p = __builtin_bit_cast(ushort2_t, p4[b]) >> 2;
 #pragma unroll
     for (int32_t u = 0; u < N; ++u) {
       const int32_t li = min(i0 + u, L - 1);
@@ -211,10 +215,15 @@ __device__ __forceinline__ void level_group(const FrameArgs &a, const uint32_t *
       key = min(key, seed_key(P[8], p4[b], 8));
       wq[b][u] = P[key & 15];
       wo[b][u] = O[key & 15];
-      const int32_t vx = x[b] + off_x(wo[b][u]), vy = y[b] + off_y(wo[b][u]);
+      // a coordinate below 0 wraps past every exemplar's last texel
+      const ushort2_t v = p + __builtin_bit_cast(ushort2_t, wo[b][u]);
+      const uint32_t vin = __builtin_bit_cast(
+          uint32_t, __builtin_elementwise_min(v, __builtin_bit_cast(ushort2_t, last)));
       // non-short-circuit: keeps the group one straight-line block
-      ok[b][u] = (i0 + u < L) & (key != INT32_MAX) & (uint32_t(vx) < sw) & (uint32_t(vy) < sh);
-      g[b][u] = ok[b][u] ? __umul24(uint32_t(vy), sw) + uint32_t(vx) : 0u;
+      ok[b][u] = (i0 + u < L) & (key != INT32_MAX) & (vin == __builtin_bit_cast(uint32_t, v));
+      const uint32_t at =
+          __builtin_amdgcn_udot2(v, __builtin_bit_cast(ushort2_t, row), 0u, false);
+      g[b][u] = ok[b][u] ? at : 0u;
     }
   }
   uint32_t ls[B][N];
@@ -235,7 +244,8 @@ __device__ __forceinline__ void level_group(const FrameArgs &a, const uint32_t *
           error_below<FMT>(gt[b], guide_unpack<FMT>(g[b][u]), a.threshold, a.wt02, a.wt1);
       const bool same = !SEG || ls[b][u] == lt[b];
       const bool take = (!done[b]) & ok[b][u] & below & same;
-      chunk[b] = take ? chunk_code(i0 + u, wq[b][u]) : chunk[b];
+      seed[b] = take ? wq[b][u] : seed[b];
+      level[b] = take ? uint32_t(i0 + u) : level[b];
       off[b] = take ? wo[b][u] : off[b];
       done[b] = done[b] || take;
     }
@@ -391,15 +401,17 @@ __device__ inline void assign_block(const FrameArgs &a, int32_t bx0, int32_t by0
   // for the pixels that end up needing them (a large table is mostly cold,
   // and few pixels fall back)
   const bool eager = a.lut_log2 <= 18;
-  uint32_t own[B], chunk[B], off[B];
+  uint32_t own[B], seed[B], level[B], off[B];
   short2_t p4[B];
   bool done[B];
+  const uint32_t last = pack_xy(uint32_t(a.sw - 1), uint32_t(a.sh - 1));
+  const uint32_t row = pack_xy(1u, uint32_t(a.sw));
 #pragma unroll
   for (int32_t b = 0; b < B; ++b) {
     own[b] = 0;
     if (eager) own[b] = glb(own_table<SEG>(a, lt[b]))[lut_bin<FMT>(gt[b], a.lut_shift, a.lut_bits)];
     p4[b] = __builtin_bit_cast(short2_t, pack_xy(uint32_t(4 * x[b]), uint32_t(4 * y[b])));
-    chunk[b] = off[b] = 0;
+    seed[b] = level[b] = off[b] = 0;
     done[b] = !in[b];
   }
   // groups of G levels (one round trip of gathers each) until every pixel of
@@ -409,17 +421,18 @@ __device__ inline void assign_block(const FrameArgs &a, int32_t bx0, int32_t by0
 #pragma unroll
     for (int32_t b = 0; b < B; ++b) all = all && done[b];
     if (__all(all)) break;
-    level_group<FMT, G, B, SEG>(a, lpos, loff, i0, x, y, p4, gt, lt, chunk, off, done);
+    level_group<FMT, G, B, SEG>(a, lpos, loff, i0, p4, gt, lt, last, row, seed, level, off, done);
   }
 #pragma unroll
   for (int32_t b = 0; b < B; ++b) {
     if (!in[b]) continue;
+    uint32_t chunk = chunk_code(int32_t(level[b]), seed[b]);
     if (!done[b]) {  // no level accepted: the pixel's own lookup
       if (!eager) own[b] = glb(own_table<SEG>(a, lt[b]))[lut_bin<FMT>(gt[b], a.lut_shift, a.lut_bits)];
-      chunk[b] = (uint32_t(L) << 26) | (uint32_t(y[b]) << 13) | uint32_t(x[b]);
+      chunk = (uint32_t(L) << 26) | (uint32_t(y[b]) << 13) | uint32_t(x[b]);
       off[b] = pack_off(int32_t(own[b] & 0xFFFFu) - x[b], int32_t(own[b] >> 16) - y[b]);
     }
-    glb(a.out_chunk)[pidx[b]] = chunk[b];
+    glb(a.out_chunk)[pidx[b]] = chunk;
     glb(a.offsets)[pidx[b]] = vote_distance(a, off[b]);
     if (a.out_nnf)
       glb(a.out_nnf)[pidx[b]] =
