@@ -110,3 +110,26 @@ def test_8bit_table(sb, channels, bits, spread, weights):
     st = sb.Style(rgb, g, bits, weights=weights)
     want = oracle.lut_build(g, bits, weights) if channels == 3 else oracle.lut_build(g, bits)
     np.testing.assert_array_equal(st.lut.cpu().numpy().view(np.uint32), want)
+
+
+# source widths on and off multiples of four, one texel, rows shorter than four
+@pytest.mark.parametrize("sw,sh,offset", [(1, 1, 0), (3, 2, 0), (4, 3, 0), (5, 4, 0), (64, 5, 0),
+                                          (62, 33, 0), (64, 9, 1)])
+def test_padded_exemplar(sb, sw, sh, offset):
+    """The packed exemplar: texels R | G << 8 | B << 16 | 1 << 24 inside an
+    empty margin of 8, zero rows after it; `offset`: the bytes start unaligned."""
+    import torch
+
+    rng = np.random.default_rng(sw * 100 + sh)
+    buf = torch.from_numpy(rng.integers(0, 256, sw * sh * 3 + offset).astype(np.uint8)).cuda()
+    n = int(sb.lib().sb_exemplar_texels(sw, sh))
+    out = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    print(f"[gpu-case] padded exemplar {sw}x{sh} +{offset}", flush=True)
+    rc = sb.lib().sb_pack_exemplar(buf.data_ptr() + offset, sw, sh, out.data_ptr(), None)
+    assert rc == sb.SB_OK
+    torch.cuda.synchronize()
+    rgb = buf.cpu().numpy()[offset:].reshape(sh, sw, 3).astype(np.uint32)
+    want = np.zeros(n, np.uint32)
+    rows = want[:n // (sw + 16) * (sw + 16)].reshape(-1, sw + 16)
+    rows[8:8 + sh, 8:8 + sw] = rgb[..., 0] | rgb[..., 1] << 8 | rgb[..., 2] << 16 | 1 << 24
+    np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want)
