@@ -135,9 +135,9 @@ int sb_batch_run(sb_batch *b, const sb_frame *frames, int32_t n, void *workspace
       return SB_EINVAL;
     // graphs: the batch's seed pass is one persistent launch over every
     // frame, so each record is built once there rather than per block;
-    // direct launches keep single frames' choice (records made in the level
-    // loop for 8-bit styles), which saves a pass and its wait
-    if (b->use_graph && !srch) a.own_seeds = 0;
+    // direct launches make the records of plain 8-bit styles in the level
+    // loop as single frames do, which may save the pass and its wait
+    if (!srch && (b->use_graph || a.fmt != SB_GUIDE_U8X2 || a.tgt_labels)) a.own_seeds = 0;
     carve_workspace(&a, ws);
     ws += align256(sb_workspace_bytes(fr.w, fr.h, &fr.params));
   }

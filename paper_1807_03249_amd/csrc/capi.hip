@@ -114,12 +114,17 @@ bool fill_frame(const sb_style *style, const void *tgt_guide, int32_t w, int32_t
   resolve_weights(style->fmt, style->weights, wt);  // checked by style_ok
   a->wt02 = uint32_t(wt[0]) | (uint32_t(wt[2]) << 16);
   a->wt1 = wt[1];
-  // records made in the level loop cost a table lookup per block and cell;
-  // worth it when the one table (256 KiB) stays in cache and blocks hold
-  // whole cells, otherwise a separate pass builds each record once
+  // records made in the level loop cost a table lookup per region of blocks
+  // and cell, a pass of their own a launch and three round trips: where blocks
+  // hold whole cells the level loop makes them, always from a small table
+  // (8-bit two-channel styles, 256 KiB), and else on frames that the pass would
+  // hold up more than the lookups (320 x 240 appearance 14.1 us, with the pass
+  // 18.8; 640 x 480 texture coordinates 16.5 and 19.9; 1080p 44.6 and 46.2, with
+  // labels 54.1 and 56.4; 4K 140 and 135, with labels 165 and 161)
   const Levels &lv = a->lv;
-  a->own_seeds = style->fmt == SB_GUIDE_U8X2 && tgt_labels == nullptr &&
-                 (lv.count == 0 || lv.log2_spacing[lv.count - 1] >= 3);
+  a->own_seeds = (lv.count == 0 || lv.log2_spacing[lv.count - 1] >= 3) &&
+                 ((style->fmt == SB_GUIDE_U8X2 && tgt_labels == nullptr) ||
+                  (!fmt_search(style->fmt) && int64_t(w) * h <= 3 << 20));
   if (fmt_search(style->fmt)) fill_tree_args(style, a);
   a->threshold = params->threshold;
   a->radius = params->radius;

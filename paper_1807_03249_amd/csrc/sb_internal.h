@@ -139,7 +139,7 @@ struct FrameArgs {
   uint32_t wt02;               // channel weights w0 | w2 << 16 (three-channel guides)
   int32_t wt1;                 // channel weight w1
   int32_t own_seeds;           // the block level loop makes its seed records itself
-                               // (8-bit two-channel table, finest spacing >= 8);
+                               // (finest spacing >= 8, see fill_frame);
                                // otherwise a seed pass fills the seed table first
   uint32_t threshold;
   int32_t radius;
