@@ -17,11 +17,13 @@
 struct sb_batch {
   unsigned char *desc_dev[2];
   unsigned char *desc_host[2];
+  bool readable;  // kernels may read desc_host (pinned, at the same address, word-aligned)
   hipGraph_t graph[2];
   hipGraphExec_t exec[2];
   hipEvent_t done[2];
   bool used[2];
   bool use_graph;
+  bool grid_given;  // the caller chose the graphs' grid
   uint32_t grid;
   sb::Tune tune;
   int next;
@@ -35,6 +37,33 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // unit holds, so that one with cheap tiles takes more of them (64 frames
 // 1060 us, with 12 1079 and with 8 1137).
 constexpr uint32_t kBlocksPerCu = 16;
+// Pixels per workgroup of that grid from which a graph is replayed.
+constexpr uint64_t kGraphPixels = 6144;
+
+// `words` 64-bit words of a descriptor half from pinned host memory, each read
+// at system scope, as the host left it.  Direct launches upload this way: the
+// transfer engine takes 80 KB and holds the stream up for 7 us more than a few
+// workgroups reading what the batch uses over the bus (two frames 50.6 us, 57.8
+// with the copy; a copy node of a captured graph is the faster of the two, 60.6
+// against 64.6, and stays).
+__global__ void __launch_bounds__(256) k_desc_upload(const uint64_t *host, uint64_t *dev,
+                                                     uint32_t words) {
+  for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < words; i += gridDim.x * 256u)
+    dev[i] = __hip_atomic_load(host + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The first n frames of half k to the device.
+hipError_t upload(const sb_batch *b, int k, int32_t n, hipStream_t stream) {
+  static_assert(batch_frames_offset() % 8 == 0 && sizeof(FrameArgs) % 8 == 0, "whole words");
+  if (!b->readable)
+    return hipMemcpyAsync(b->desc_dev[k], b->desc_host[k], batch_desc_bytes(),
+                          hipMemcpyHostToDevice, stream);
+  const uint32_t words = uint32_t((batch_frames_offset() + size_t(n) * sizeof(FrameArgs)) / 8);
+  k_desc_upload<<<(words + 255) / 256, 256, 0, stream>>>(
+      reinterpret_cast<const uint64_t *>(b->desc_host[k]),
+      reinterpret_cast<uint64_t *>(b->desc_dev[k]), words);
+  return hipGetLastError();
+}
 
 hipError_t batch_cleanup(sb_batch *b) {
   hipError_t first = hipSuccess;
@@ -82,6 +111,7 @@ int sb_batch_create(void *desc_dev, void *desc_host, int32_t use_graph, const sb
   if (!b) return SB_ENOMEM;
   memset(b, 0, sizeof *b);
   b->use_graph = use_graph != 0;
+  b->grid_given = blocks_per_cu > 0;
   b->tune = t;
   for (int k = 0; k < 2; ++k) {
     b->desc_dev[k] = static_cast<unsigned char *>(desc_dev) + k * batch_desc_bytes();
@@ -91,6 +121,16 @@ int sb_batch_create(void *desc_dev, void *desc_host, int32_t use_graph, const sb
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   b->grid = uint32_t(cus > 0 ? cus : 256) * uint32_t(blocks_per_cu > 0 ? blocks_per_cu : kBlocksPerCu);
+  if (e == hipSuccess) {
+    // other host memory stays with the copy
+    hipPointerAttribute_t at;
+    const uintptr_t align = reinterpret_cast<uintptr_t>(desc_dev) |
+                            reinterpret_cast<uintptr_t>(desc_host);
+    if (hipPointerGetAttributes(&at, desc_host) != hipSuccess)
+      (void)hipGetLastError();
+    else
+      b->readable = at.type == hipMemoryTypeHost && at.devicePointer == desc_host && align % 8 == 0;
+  }
   for (int k = 0; k < 2 && e == hipSuccess; ++k)
     e = hipEventCreateWithFlags(&b->done[k], hipEventDisableTiming);
   for (int k = 0; k < 2 && e == hipSuccess && b->use_graph; ++k) {
@@ -124,6 +164,14 @@ int sb_batch_run(sb_batch *b, const sb_frame *frames, int32_t n, void *workspace
   // the search formats (many-channel guides) to the per-frame kernels after
   // them on the same stream (search[0 .. ns)), each in its own workspace
   static thread_local FrameArgs args[kMaxBatchFrames], search[kMaxBatchFrames];
+  // a plan's graph replays its persistent grid whatever the batch: the uneven
+  // shares even out over several tiles per workgroup, and below that direct
+  // launches are faster (64 frames, 45 Mpixel: 1040 us and 1052 launched
+  // directly; 16 frames 302 and 285, two 60.8 and 45.7) unless the caller chose
+  // the grid
+  uint64_t px = 0;
+  for (int32_t f = 0; f < n; ++f) px += uint64_t(frames[f].w) * uint64_t(frames[f].h);
+  const bool graph = b->use_graph && (b->grid_given || px >= uint64_t(b->grid) * kGraphPixels);
   char *ws = static_cast<char *>(workspace);
   int32_t nt = 0, ns = 0;
   for (int32_t f = 0; f < n; ++f) {
@@ -137,7 +185,7 @@ int sb_batch_run(sb_batch *b, const sb_frame *frames, int32_t n, void *workspace
     // frame, so each record is built once there rather than per block;
     // direct launches make the records of plain 8-bit styles in the level
     // loop as single frames do, which may save the pass and its wait
-    if (!srch && (b->use_graph || a.fmt != SB_GUIDE_U8X2 || a.tgt_labels)) a.own_seeds = 0;
+    if (!srch && (graph || a.fmt != SB_GUIDE_U8X2 || a.tgt_labels)) a.own_seeds = 0;
     carve_workspace(&a, ws);
     ws += align256(sb_workspace_bytes(fr.w, fr.h, &fr.params));
   }
@@ -166,12 +214,12 @@ int sb_batch_run(sb_batch *b, const sb_frame *frames, int32_t n, void *workspace
   }
   memcpy(hd + batch_frames_offset(), args, size_t(nt) * sizeof(FrameArgs));
   hipError_t e = hipSuccess;
-  if (nt > 0 && b->use_graph) {
+  if (nt > 0 && graph) {
     e = hipGraphLaunch(b->exec[k], stream);
   } else if (nt > 0) {
     // direct launches know the batch's shape: exact grids, one tile per
     // workgroup, so kernels on other streams interleave with them
-    e = hipMemcpyAsync(b->desc_dev[k], hd, batch_desc_bytes(), hipMemcpyHostToDevice, stream);
+    e = upload(b, k, nt, stream);
     uint32_t totals[kBatchKinds];
     for (int kind = 0; kind < kBatchKinds; ++kind) totals[kind] = pre[kind][nt];
     if (e == hipSuccess) e = launch_batch_exact(b->desc_dev[k], totals, b->tune, stream);

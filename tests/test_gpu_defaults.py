@@ -47,3 +47,30 @@ def test_default_choice(sb, fmt, w, h, size, threshold, radius):
     want = sb.stylize(st, tgt, None, p, want_nnf=True, tune=(4, 16, 4, 4, 1))
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+# below and above the size from which a plan with a default grid replays its
+# graph, and either side of it with the grid given (a graph) or no graph at all
+@pytest.mark.parametrize("frames,graph,bpc", [(2, True, 0), (3, True, 0), (4, True, 0),
+                                              (2, True, 4), (4, False, 0)])
+def test_batch_routes(sb, frames, graph, bpc):
+    import torch
+
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(frames)
+    size, w, h = 64, 3840, 2160
+    styles = [sb.Style((torch.rand(size, size, 3, generator=gen, device="cuda") * 255).byte(),
+                       (torch.rand(size, size, 2, generator=gen, device="cuda") * 255).byte(), 6)
+              for _ in range(2)]
+    lat = torch.rand(frames, 2, h // 40 + 2, w // 40 + 2, generator=gen, device="cuda")
+    v = torch.nn.functional.interpolate(lat, (h, w), mode="bilinear")
+    guides = (v * 255).byte().permute(0, 2, 3, 1).contiguous()
+    print(f"[gpu-case] batch of {frames} graph={graph} blocks_per_cu={bpc}", flush=True)
+    plan = sb.Batch(use_graph=graph, blocks_per_cu=bpc)
+    for run in range(3):  # both descriptor halves, and one again
+        jobs = [sb.FrameJob(styles[f % 2], guides[f], None, sb.params(4, 8, 48, 3, seed=run * 9 + f))
+                for f in range(frames)]
+        plan.run(jobs)
+        for j in jobs:
+            rgb, chunk = sb.stylize(j.style, j.guide, None, j.params)
+            assert torch.equal(j.out_rgb, rgb) and torch.equal(j.out_chunk, chunk)
