@@ -133,3 +133,34 @@ def test_padded_exemplar(sb, sw, sh, offset):
     rows = want[:n // (sw + 16) * (sw + 16)].reshape(-1, sw + 16)
     rows[8:8 + sh, 8:8 + sw] = rgb[..., 0] | rgb[..., 1] << 8 | rgb[..., 2] << 16 | 1 << 24
     np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want)
+
+
+# one level, more records than lanes (9 x 11), frames of a block and a pixel
+# more, cells smaller than blocks, and no level at all
+@pytest.mark.parametrize("depth,channels,w,h,levels,finest", [
+    (8, 5, 97, 61, 1, 8), (16, 4, 97, 61, 11, 8), (8, 3, 8, 8, 4, 8), (8, 7, 17, 9, 9, 16),
+    (16, 7, 40, 33, 3, 8), (16, 2, 70, 50, 3, 4), (8, 5, 41, 23, 0, 8)])
+def test_search_level_loop(sb, depth, channels, w, h, levels, finest):
+    """Many-channel frames on both level loops, every output against the oracle."""
+    import torch
+
+    rng = np.random.default_rng(w * 100 + levels)
+    elems, dt = oracle.texel_bytes(depth, channels) * 8 // depth, np.uint8 if depth == 8 else np.uint16
+    top = (1 << depth) - 1
+
+    def guide(rows, cols):
+        y, x = np.mgrid[0:rows, 0:cols]
+        g = [(np.sin(x / (9 + k)) + np.cos(y / (7 + k)) + 2) * top / 4 for k in range(elems)]
+        return np.ascontiguousarray(np.stack(g, -1).astype(dt))
+
+    src, tgt = guide(48, 52), guide(h, w)
+    rgb = rng.integers(0, 256, (48, 52, 3)).astype(np.uint8)
+    t = (top // 16) ** 2
+    print(f"[gpu-case] search level loop {depth}x{channels} {w}x{h} L={levels} finest={finest}",
+          flush=True)
+    st = sb.Style(rgb, src, channels=channels)
+    tg = torch.from_numpy(tgt.view(np.int16) if depth == 16 else tgt).cuda()
+    got = sb.stylize(st, tg, None, sb.params(levels, finest, t, 2, seed=5), want_nnf=True)
+    want = oracle.stylize_n(rgb, src, channels, tgt, None, levels, finest, t, 2, seed=5)
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a.cpu().numpy().view(b.dtype).reshape(b.shape), b)
