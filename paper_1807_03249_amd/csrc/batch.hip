@@ -166,7 +166,7 @@ int sb_batch_run(sb_batch *b, const sb_frame *frames, int32_t n, void *workspace
   static thread_local FrameArgs args[kMaxBatchFrames], search[kMaxBatchFrames];
   // a plan's graph replays its persistent grid whatever the batch: the uneven
   // shares even out over several tiles per workgroup, and below that direct
-  // launches are faster (64 frames, 45 Mpixel: 1040 us and 1052 launched
+  // launches are faster (64 frames, 45 Mpixel: 1019 us and 1028 launched
   // directly; 16 frames 302 and 285, two 60.8 and 45.7) unless the caller chose
   // the grid
   uint64_t px = 0;

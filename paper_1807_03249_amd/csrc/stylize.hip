@@ -1014,8 +1014,14 @@ __global__ void __launch_bounds__(256) k_batch_seeds(const unsigned char *__rest
   });
 }
 
+// The default choices are scheduled for the waves per SIMD that their registers
+// allow anyway (72, three values in scratch, and 80): 64 frames 1019 us as a
+// graph and 1028 launched directly, 1040 and 1053 without the hint (with one
+// wave more each 1006 directly, but 1084 as a graph).
 template <int G, int B>
-__global__ void __launch_bounds__(256) k_batch_assign(const unsigned char *__restrict__ desc) {
+__global__ void __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(G == 2 && B == 2 ? 7 : 1)))
+    k_batch_assign(const unsigned char *__restrict__ desc) {
   batch_loop<1, 256, 4 * wave_recs_words(B)>(desc, [](const FrameArgs &fa, uint32_t local,
                                                      uint32_t *w) __attribute__((always_inline)) {
     const bool seg = fa.tgt_labels != nullptr;
@@ -1033,7 +1039,9 @@ __global__ void __launch_bounds__(256) k_batch_assign(const unsigned char *__res
 }
 
 template <int PPT, int TH, int RLO, int RHI, bool SPLIT>
-__global__ void __launch_bounds__(16 * TH) k_batch_blend(const unsigned char *__restrict__ desc) {
+__global__ void __launch_bounds__(16 * TH)
+    __attribute__((amdgpu_waves_per_eu(RLO == 0 && !SPLIT ? 6 : 1)))
+    k_batch_blend(const unsigned char *__restrict__ desc) {
   constexpr int WORDS = blend_tile_words(PPT, TH, RHI, SPLIT);
   batch_loop<RLO == 0 ? 2 : 3, 16 * TH, WORDS>(desc, [](const FrameArgs &fa, uint32_t local,
                                                         uint32_t *w)
