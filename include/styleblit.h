@@ -232,7 +232,8 @@ int sb_style_destroy(sb_style *style);
  *   u*(g) = argmin_u sum_k w_k (g_k - G_S[u]_k)^2, ties to the smallest
  *   raster index of u,
  * over the raw channel values (no quantisation), with the style's weights.
- * The search runs on a balanced k-d tree of the source guide built on the
+ * The search runs on a balanced k-d tree of the source guide's distinct texels
+ * (of those equal in every channel the one of smallest raster index) built on the
  * device: eight children per node, every child with the tight bounding box of
  * its texels and its smallest raster index, splits at the median of the widest
  * (weighted) channel.  A search skips a child only when its box lies strictly

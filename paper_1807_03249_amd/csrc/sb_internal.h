@@ -56,12 +56,16 @@ __host__ __device__ constexpr int32_t search_texel_bytes(int32_t fmt, int32_t ch
 // 8-ary tree of `levels` levels below the root, the smallest number with
 // 8^levels >= n, in level order: node p of level d is entry tree_start(d) +
 // p, its children the entries 8 p .. 8 p + 7 of level d + 1, and the entries
-// of the last level are the texels.  Three sections: per node above the last
+// of the last level are the texels.  Texels equal in every channel are one, so
+// the m <= n distinct ones fill the last level's first places and the tree that
+// is searched begins at node 0 of the level from which 8^k >= m.  After a header
+// (entries, m, texel bytes, channels) three sections: per node above the last
 // but one level its children's boxes, the eight lowest values of every
 // element and then the eight highest (16 texels); the texels; and per entry a
 // key, the smallest source coordinate (x | y << 16: y << 16 | x orders like
 // the raster index) of its texels, kNoTreeKey for the entries past a level's
 // last node, up to a multiple of eight.
+constexpr size_t kTreeHeader = 256;
 constexpr uint32_t kNoTreeKey = 0xFFFFFFFFu;
 __host__ __device__ constexpr uint32_t tree_start(int32_t d) {
   return 0x49249249u & ((1u << (3 * d)) - 1u);  // (8^d - 1) / 7, d <= 10
@@ -77,7 +81,7 @@ inline TreeLayout tree_layout(size_t n, size_t t) {
   l.levels = 1;
   while ((size_t(1) << (3 * l.levels)) < n) ++l.levels;
   l.entries = tree_start(l.levels) + uint32_t((n + 7) & ~size_t(7));
-  l.boxes = 256;
+  l.boxes = kTreeHeader;
   l.vals = l.boxes + al(size_t(tree_start(l.levels - 1)) * 16 * t);
   l.keys = l.vals + al(((n + 7) & ~size_t(7)) * t);
   // callers size the buffer as they did for two linked nodes of 2t + 8 bytes
@@ -161,7 +165,7 @@ struct FrameArgs {
   // 0 past the guide's channels)
   const void *t_boxes;
   const uint32_t *t_keys;
-  uint32_t t_vals, t_last;
+  uint32_t t_vals;
   int32_t t_levels;
   int32_t texel;
   uint32_t wn[2];

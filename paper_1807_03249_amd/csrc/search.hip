@@ -3,7 +3,9 @@
 // additional guiding channels of Sec. 3.1, for which the paper suggests a
 // search tree.
 //
-//   tree build   a balanced k-d tree of the source guide, kept as a complete
+//   tree build   texels equal in every channel become one, the one of smallest
+//                raster index (k_tree_merge, k_tree_take); of the distinct
+//                ones a balanced k-d tree, kept as a complete
 //                8-ary tree in level order (see tree_layout): every split is
 //                at the median of the widest element (by weight, then by raw
 //                range) and hands its left child exactly half of the padded
@@ -235,20 +237,32 @@ __device__ __forceinline__ uint32_t pack_dist(uint64_t d) {
   return __builtin_bit_cast(uint32_t, f) >> 2;
 }
 
-struct TreeView {
+struct TreeRef {
   const void *boxes;
   const uint32_t *keys;
   uint32_t vals;  // bytes from the boxes to the texels
-  uint32_t last;  // the last texel
   int32_t levels;
 };
 
-TreeView tree_view(const void *tree, size_t n, size_t t) {
+TreeRef tree_ref(const void *tree, size_t n, size_t t) {
   const TreeLayout l = tree_layout(n, t);
   const char *b = static_cast<const char *>(tree);
-  return TreeView{b + l.boxes, reinterpret_cast<const uint32_t *>(b + l.keys),
-                  uint32_t(l.vals - l.boxes), uint32_t(n - 1), l.levels};
+  return TreeRef{b + l.boxes, reinterpret_cast<const uint32_t *>(b + l.keys),
+                 uint32_t(l.vals - l.boxes), l.levels};
 }
+
+// ... and what only the header tells: the last texel, and the level of the node
+// that holds them all (a guide of few values is searched in as many steps as one
+// of few texels).
+struct TreeView : TreeRef {
+  uint32_t last;
+  int32_t top;
+  __device__ __forceinline__ explicit TreeView(const TreeRef &r) : TreeRef(r) {
+    const SB_GLOBAL unsigned char *b = glb(static_cast<const unsigned char *>(boxes));
+    last = reinterpret_cast<const SB_GLOBAL uint32_t *>(b - kTreeHeader)[1] - 1u;
+    top = levels - max((34 - int32_t(__clz(int(last)))) / 3, 1);
+  }
+};
 
 // N texels from p on (dword-aligned vectors).
 template <int S, int N>
@@ -336,10 +350,10 @@ struct Search {
   uint32_t best_key, pos, left[N];
   int32_t depth;
 
-  __device__ __forceinline__ void start(const Tx<S> &t, Dist b, uint32_t k) {
+  __device__ __forceinline__ void start(const TreeView &tv, const Tx<S> &t, Dist b, uint32_t k) {
     q = to_pairs<D, S>(t);
     best = b, best_key = k;
-    pos = 0u, depth = 0;
+    pos = 0u, depth = tv.top;
 #pragma unroll
     for (int j = 0; j < N; ++j) left[j] = kGone;
   }
@@ -448,7 +462,7 @@ __device__ uint32_t tree_search(const TreeView &tv, const Tx<S> &q, const uint32
   const Weights<D, S> wt(wn);
   uint32_t *slots = lane_slots<G>(tv, stack);
   Search<D, S, G> s;
-  s.start(q, ~Dist(0), kNoTreeKey);
+  s.start(tv, q, ~Dist(0), kNoTreeKey);
   while (!s.step(tv, wt, slots)) {
   }
   return s.best_key;
@@ -461,16 +475,11 @@ __device__ uint32_t tree_search(const TreeView &tv, const Tx<S> &q, const uint32
 template <int D, int S>
 constexpr uint32_t kBoxWords = 2 * kElems<D, S>;
 
-// The texels of the splits so far: from a split's output, or (keys null) the
-// guide in raster order.
+// The distinct texels in the order of the splits so far, and their number.
 struct TexelsIn {
   const void *vals;
-  const uint32_t *keys;
-  uint32_t n, sw;
+  const uint32_t *keys, *n;
 };
-__device__ __forceinline__ uint32_t texel_key(const TexelsIn &t, uint32_t i) {
-  return t.keys ? glb(t.keys)[i] : ((i / t.sw) << 16) | (i % t.sw);
-}
 
 struct SplitArgs {
   TexelsIn in;
@@ -564,8 +573,8 @@ struct Box {
   }
 };
 
-// Clears what the build accumulates into: `ones` words of all ones at a and
-// at b, zeros at c.
+// Clears what the build accumulates into: words of all ones at a and at b,
+// zeros at c.
 __global__ void __launch_bounds__(256) k_tree_clear(uint32_t *a, uint32_t na, uint32_t *b,
                                                     uint32_t nb, uint32_t *c, uint32_t nc) {
   const uint32_t step = gridDim.x * 256u, first = blockIdx.x * 256u + threadIdx.x;
@@ -574,19 +583,117 @@ __global__ void __launch_bounds__(256) k_tree_clear(uint32_t *a, uint32_t na, ui
   for (uint32_t i = first; i < nc; i += step) glb(c)[i] = 0u;
 }
 
-// The whole guide's box.
-template <int D, int S>
-__global__ void __launch_bounds__(256) k_tree_box(const void *guide, uint32_t n, uint32_t *box) {
-  __shared__ uint32_t words[kBoxWords<D, S>];
-  const uint32_t tid = threadIdx.x;
-  if (tid < kBoxWords<D, S>) words[tid] = 0xFFFFFFFFu;
+// The table that equal texels meet in, by open addressing: per slot the smallest
+// raster index of one value's texels, all ones where empty.
+struct MergeArgs {
+  const void *guide;
+  uint32_t n, sw;
+  uint32_t *table;
+  uint32_t slots;    // a power of two, at least 3 n
+  uint32_t mask[4];  // the channels' bits of a texel's words
+  uint8_t *dup;      // per texel: 1 where an equal one has a smaller index
+};
+constexpr uint32_t kNoTexel = 0xFFFFFFFFu;
+constexpr uint32_t kMergeThreads = 1024;
+
+template <int S>
+__device__ __forceinline__ bool same_texel(const Tx<S> &a, const Tx<S> &b, const uint32_t *mask) {
+  uint32_t x = 0;
+#pragma unroll
+  for (int k = 0; k < S / 4; ++k) x |= (a.w[k] ^ b.w[k]) & mask[k];
+  return x == 0u;
+}
+
+// Texels equal in every channel are one to a search, and a tree that holds each
+// many times has whole levels of boxes at one distance, all of which a lookup has
+// to enter (a constant 512 x 512 guide: 65536 lookups 202 us, 11 with one texel).
+// So every texel but the first of its value is marked: whenever two equal ones
+// meet, the one of larger index.  The texels of a workgroup meet in LDS first (the
+// smallest index of each hash's place there, so a texel equal to that one is done):
+// a constant region sends one of a workgroup's 1024 to the slot that all of them
+// share, where atomics follow one another at 16 ns.  A probe that finds another
+// value's slot goes on by an odd step of the hash; a quarter of the slots or fewer
+// are ever taken, so a wave's longest chain is about three.
+template <int S>
+__global__ void __launch_bounds__(kMergeThreads) k_tree_merge(MergeArgs a) {
+  __shared__ uint32_t first[kMergeThreads];
+  const uint32_t tid = threadIdx.x, i = blockIdx.x * kMergeThreads + tid;
+  const Tx<S> t = load_tx<S>(a.guide, min(i, a.n - 1u));
+  uint32_t h = 0;
+#pragma unroll
+  for (int k = 0; k < S / 4; ++k) {
+    h = (h ^ (t.w[k] & a.mask[k])) * 0x9E3779B1u;  // 2^32 over the golden ratio
+    h ^= h >> 15;
+  }
+  h *= 0x9E3779B1u;
+  h ^= h >> 16;
+  first[tid] = kNoTexel;
   __syncthreads();
+  uint32_t *place = &first[(h >> 16) % kMergeThreads];
+  if (i < a.n) atomicMin(place, i);
+  __syncthreads();
+  if (i >= a.n) return;
+  const uint32_t f = *place;
+  if (f != i && same_texel<S>(load_tx<S>(a.guide, f), t, a.mask)) {
+    a.dup[i] = 1;
+    return;
+  }
+  for (uint32_t s = h;; s += (h >> 12) | 1u) {
+    uint32_t *slot = a.table + (s & (a.slots - 1u));
+    uint32_t v = atomicCAS(slot, kNoTexel, i);
+    if (v == kNoTexel) return;
+    if (!same_texel<S>(load_tx<S>(a.guide, v), t, a.mask)) continue;
+    v = atomicMin(slot, i);  // the slot is the value's for good, its index falls
+    a.dup[max(v, i)] = 1;
+    return;
+  }
+}
+
+// The unmarked texels one after another (in raster order within a workgroup's:
+// texels that a split cannot tell apart stay beside their neighbours), with their
+// coordinates and (with `box`) the box of them all.
+constexpr uint32_t kTakePer = 4;
+template <int D, int S>
+__global__ void __launch_bounds__(256) k_tree_take(MergeArgs a, void *vals, uint32_t *keys,
+                                                   uint32_t *count, uint32_t *box) {
+  __shared__ uint32_t words[kBoxWords<D, S>], wave_n[4], base;
+  const uint32_t tid = threadIdx.x, wave = tid >> 6;
+  if (tid < kBoxWords<D, S>) words[tid] = 0xFFFFFFFFu;
+  const uint32_t i0 = (blockIdx.x * 4u + wave) * (64u * kTakePer) + (tid & 63u);
+  uint32_t at[kTakePer], n = 0;
+  bool has[kTakePer];
+  Tx<S> t[kTakePer];
+#pragma unroll
+  for (uint32_t k = 0; k < kTakePer; ++k) {
+    const uint32_t i = min(i0 + 64u * k, a.n - 1u);
+    t[k] = load_tx<S>(a.guide, i);
+    has[k] = i0 + 64u * k < a.n && glb(a.dup)[i] == 0;
+  }
+#pragma unroll
+  for (uint32_t k = 0; k < kTakePer; ++k) {
+    const uint64_t m = __ballot(has[k]);
+    at[k] = n + __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32),
+                                          __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
+    n += uint32_t(__popcll(m));
+  }
+  if ((tid & 63u) == 0) wave_n[wave] = n;
+  __syncthreads();
+  if (tid == 0) base = atomicAdd(count, wave_n[0] + wave_n[1] + wave_n[2] + wave_n[3]);
+  __syncthreads();
+  uint32_t from = base;
+  for (uint32_t w = 0; w < wave; ++w) from += wave_n[w];
   Box<D, S> b;
   b.clear();
-  for (uint32_t i = blockIdx.x * 256u + tid; i < n; i += gridDim.x * 256u) {
-    const Pairs<D, S> p = to_pairs<D, S>(load_tx<S>(guide, i));
+#pragma unroll
+  for (uint32_t k = 0; k < kTakePer; ++k) {
+    if (!has[k]) continue;
+    const uint32_t i = i0 + 64u * k;
+    store_tx<S>(vals, from + at[k], t[k]);
+    glb(keys)[from + at[k]] = ((i / a.sw) << 16) | (i % a.sw);
+    const Pairs<D, S> p = to_pairs<D, S>(t[k]);
     b.add(p, p);
   }
+  if (!box) return;
   b.join_lanes(64);
   if ((tid & 63u) == 0) b.widen(words);
   __syncthreads();
@@ -599,11 +706,11 @@ template <int D, int S>
 struct Segment {
   uint32_t id, first, count, half, lo;
   int32_t axis, shift;
-  __device__ __forceinline__ explicit Segment(const SplitArgs &a) {
+  __device__ __forceinline__ Segment(const SplitArgs &a, uint32_t n) {
     const uint32_t seg = blockIdx.x >> (a.lg - int32_t(kSplitLog));
     id = (1u << a.level) - 1u + seg;
     first = seg << a.lg;
-    count = min(a.in.n - first, 1u << a.lg);
+    count = min(n - first, 1u << a.lg);
     half = 1u << (a.lg - 1);
     const SB_GLOBAL uint32_t *box = glb(a.boxes) + size_t(id) * kBoxWords<D, S>;
     uint32_t l[kElems<D, S>], h[kElems<D, S>];
@@ -631,7 +738,9 @@ constexpr uint32_t kSplitPer = kSplitBlock / kSplitThreads;
 template <int D, int S>
 __global__ void __launch_bounds__(kSplitThreads) k_tree_hist(SplitArgs a) {
   __shared__ uint32_t bins[kBins];
-  const Segment<D, S> sg(a);
+  const uint32_t n = glb(a.in.n)[0];
+  if (blockIdx.x * kSplitBlock >= n) return;
+  const Segment<D, S> sg(a, n);
   if (sg.count <= sg.half) return;  // all of it goes left
   const uint32_t tid = threadIdx.x;
 #pragma unroll
@@ -641,10 +750,10 @@ __global__ void __launch_bounds__(kSplitThreads) k_tree_hist(SplitArgs a) {
   Tx<S> t[kSplitPer];
 #pragma unroll
   for (uint32_t k = 0; k < kSplitPer; ++k)
-    t[k] = load_tx<S>(a.in.vals, min(i0 + kSplitThreads * k, a.in.n - 1));
+    t[k] = load_tx<S>(a.in.vals, min(i0 + kSplitThreads * k, n - 1));
 #pragma unroll
   for (uint32_t k = 0; k < kSplitPer; ++k)
-    if (i0 + kSplitThreads * k < a.in.n) atomicAdd(&bins[sg.bin(t[k])], 1u);
+    if (i0 + kSplitThreads * k < n) atomicAdd(&bins[sg.bin(t[k])], 1u);
   __syncthreads();
 #pragma unroll
   for (uint32_t k = 0; k < kBins; k += kSplitThreads)
@@ -663,7 +772,9 @@ __global__ void __launch_bounds__(kSplitThreads) k_tree_split(SplitArgs a) {
   constexpr uint32_t W = kSplitThreads / 64;
   __shared__ uint32_t part[W], found[3], wave_n[W][3], base[3];
   __shared__ uint32_t box[2 * kBoxWords<D, S>];
-  const Segment<D, S> sg(a);
+  const uint32_t total = glb(a.in.n)[0];
+  if (blockIdx.x * kSplitBlock >= total) return;
+  const Segment<D, S> sg(a, total);
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   if (tid < 2 * kBoxWords<D, S>) box[tid] = 0xFFFFFFFFu;
   const uint32_t i0 = blockIdx.x * kSplitBlock + tid;
@@ -671,9 +782,9 @@ __global__ void __launch_bounds__(kSplitThreads) k_tree_split(SplitArgs a) {
   uint32_t key[kSplitPer];
 #pragma unroll
   for (uint32_t k = 0; k < kSplitPer; ++k) {
-    const uint32_t i = min(i0 + kSplitThreads * k, a.in.n - 1);
+    const uint32_t i = min(i0 + kSplitThreads * k, total - 1);
     t[k] = load_tx<S>(a.in.vals, i);
-    key[k] = texel_key(a.in, i);
+    key[k] = glb(a.in.keys)[i];
   }
   uint32_t mid = kBins, below = sg.count, same = 0u;  // all left
   if (sg.count > sg.half) {
@@ -707,7 +818,7 @@ __global__ void __launch_bounds__(kSplitThreads) k_tree_split(SplitArgs a) {
   for (uint32_t k = 0; k < kSplitPer; ++k) {
     const uint32_t b = sg.bin(t[k]);
     // 0 below the median's bin, 1 in it, 2 above, 3 no texel
-    cls[k] = i0 + kSplitThreads * k >= a.in.n ? 3u : b < mid ? 0u : b == mid ? 1u : 2u;
+    cls[k] = i0 + kSplitThreads * k >= total ? 3u : b < mid ? 0u : b == mid ? 1u : 2u;
     rank[k] = 0u;
 #pragma unroll
     for (uint32_t c = 0; c < 3; ++c) {
@@ -850,7 +961,9 @@ __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
   __shared__ uint32_t wkey[8];
   constexpr uint32_t kNone = 0xFFFFFFFFu;  // past the last texel: sorts behind every one
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  const uint32_t first = blockIdx.x * kSortBlock, count = min(a.in.n - first, kSortBlock);
+  const uint32_t n = glb(a.in.n)[0], first = blockIdx.x * kSortBlock;
+  if (first >= n) return;
+  const uint32_t count = min(n - first, kSortBlock);
 #pragma unroll
   for (uint32_t k = 0; k < kSortBlock; k += 512) {
     const uint32_t i = k + tid;
@@ -894,7 +1007,7 @@ __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
     const uint32_t v = st.v[j];
     if (v == kNone) continue;
     const Tx<S> t = tex[v & (kSortBlock - 1u)];
-    const uint32_t key = texel_key(a.in, first + (v & (kSortBlock - 1u)));
+    const uint32_t key = glb(a.in.keys)[first + (v & (kSortBlock - 1u))];
     store_tx<S>(a.vals, first + 4 * tid + j, t);
     glb(a.keys)[tree_start(a.levels) + first + 4 * tid + j] = key;
     const Pairs<D, S> p = to_pairs<D, S>(t);
@@ -930,8 +1043,9 @@ __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
 // are read), and the header.
 template <int D, int S>
 __global__ void __launch_bounds__(1024) k_tree_top(void *boxes, uint32_t *keys, int32_t levels,
-                                                   uint32_t n, uint32_t *header,
+                                                   const uint32_t *count, uint32_t *header,
                                                    uint32_t channels) {
+  const uint32_t n = glb(count)[0];
   for (int32_t up = 4; up < levels; ++up) {
     const uint32_t kids = uint32_t((uint64_t(n) + (1ull << (3 * up - 3)) - 1) >> (3 * up - 3));
     const uint32_t from = tree_start(levels - up + 1), to = tree_start(levels - up);
@@ -952,7 +1066,7 @@ __global__ void __launch_bounds__(1024) k_tree_top(void *boxes, uint32_t *keys, 
     }
     __syncthreads();
   }
-  // header: entries, texels, texel bytes, channels (for inspection only)
+  // (searches read the number of texels)
   if (threadIdx.x == 0) {
     glb(header)[0] = tree_start(levels) + n;
     glb(header)[1] = n;
@@ -964,7 +1078,7 @@ __global__ void __launch_bounds__(1024) k_tree_top(void *boxes, uint32_t *keys, 
 // ------------------------------------------------------------- frame passes
 
 __device__ inline TreeView frame_tree(const FrameArgs &a) {
-  return TreeView{a.t_boxes, a.t_keys, a.t_vals, a.t_last, a.t_levels};
+  return TreeView(TreeRef{a.t_boxes, a.t_keys, a.t_vals, a.t_levels});
 }
 
 // Record idx of the padded seed table: the seed of its cell and the
@@ -1215,7 +1329,7 @@ __global__ void __launch_bounds__(256) k_fallback_n(FrameArgs a) {
   const Weights<D, S> wt(a.wn);
   uint32_t *slots = lane_slots<G>(tv, stack);
   Search<D, S, G> s;
-  s.start(Tx<S>{}, 0, 0u);
+  s.start(tv, Tx<S>{}, 0, 0u);
   uint32_t xy = 0, pidx = 0;
   bool busy = false;
   for (;;) {
@@ -1265,7 +1379,7 @@ __global__ void __launch_bounds__(256) k_fallback_n(FrameArgs a) {
         const Entry en = queue[(head + rank) % kFallbackQueue];
         xy = en.xy;
         pidx = __umul24(xy >> 16, uint32_t(a.w)) + (xy & 0xFFFFu);
-        s.start(load_tx<S>(a.tgt_guide, pidx), en.dist, en.key);
+        s.start(tv, load_tx<S>(a.tgt_guide, pidx), en.dist, en.key);
       }
       wave_lds_sync();
       const uint32_t took = min(waiting, fill);
@@ -1287,13 +1401,14 @@ __global__ void __launch_bounds__(256) k_fallback_n(FrameArgs a) {
 
 // G lanes per query texel.
 template <int D, int S, int G>
-__global__ void __launch_bounds__(256) k_tree_query(TreeView tv, const void *q, uint32_t n,
+__global__ void __launch_bounds__(256) k_tree_query(TreeRef tree, const void *q, uint32_t n,
                                                     uint32_t *out, uint32_t w0, uint32_t w1) {
   extern __shared__ uint32_t stack[];
   const uint64_t i = (uint64_t(blockIdx.x) * 256 + threadIdx.x) / G;
   if (i >= n) return;
   const uint32_t wn[2] = {w0, w1};
-  const uint32_t u = tree_search<D, S, G>(tv, load_tx<S>(q, uint32_t(i)), wn, stack);
+  const uint32_t u = tree_search<D, S, G>(TreeView(tree), load_tx<S>(q, uint32_t(i)), wn,
+                                          stack);
   if ((threadIdx.x & uint32_t(G - 1)) == 0) glb(out)[i] = u;
 }
 
@@ -1331,22 +1446,30 @@ unsigned blocks_for(uint64_t n, unsigned bs) { return unsigned((n + bs - 1) / bs
 bool side_ok(int32_t v) { return v >= 1 && v <= SB_MAX_SIDE; }
 
 // The build's workspace: the texels and keys of two consecutive levels of
-// splits, and per segment of the levels split over the chip its box, its
-// histogram and its counters.
+// splits, the table of distinct texels, per segment of the levels split over the
+// chip its box, its histogram and its counters, the number of distinct texels and
+// the marks of the others.
 struct BuildWs {
   void *vals[2];
   uint32_t *keys[2];
-  uint32_t *boxes, *hist, *ctr;
-  uint32_t box_words, hist_words;  // hist and ctr together
-  int32_t splits;                  // levels split over the chip
+  uint32_t *table, *boxes, *hist, *ctr, *count;
+  uint8_t *dup;
+  uint32_t slots, box_words, zero_words;  // (zero: hist, ctr, count and dup)
+  int32_t splits;                         // levels split over the chip
   size_t total;
 };
 
-BuildWs build_ws(char *base, size_t n, size_t t, size_t box_words) {
+BuildWs build_ws(char *base, size_t n, size_t t) {
+  constexpr size_t kWidest = 16;  // box words of eight elements
   BuildWs w;
   w.splits = 0;
   while ((size_t(kSortBlock) << w.splits) < n) ++w.splits;
   const size_t segs = (size_t(1) << w.splits) - 1;  // at most n / 1024
+  size_t slots = 2;
+  while (slots < 3 * n) slots *= 2;
+  w.slots = uint32_t(slots);
+  w.box_words = uint32_t(segs * kWidest);
+  w.zero_words = uint32_t(segs * (kBins + 4) + 1 + (n + 3) / 4);
   size_t at = 0;
   auto take = [&](size_t bytes) {
     char *p = base ? base + at : nullptr;
@@ -1355,17 +1478,15 @@ BuildWs build_ws(char *base, size_t n, size_t t, size_t box_words) {
   };
   for (int k = 0; k < 2; ++k) w.vals[k] = take(n * t);
   for (int k = 0; k < 2; ++k) w.keys[k] = reinterpret_cast<uint32_t *>(take(n * 4));
-  // 40 bytes per texel for the segments' data, which need less than 5
-  char *seg = take(n * 16);
-  take(n * 16);
-  take(n * 8);
-  take(256);
+  // the table and the boxes, cleared to ones in one run, lie one after the other
+  char *p = take((slots + w.box_words + w.zero_words) * 4);
   w.total = at;
-  w.box_words = uint32_t(segs * box_words);
-  w.hist_words = uint32_t(segs * (kBins + 4));
-  w.boxes = reinterpret_cast<uint32_t *>(seg);
-  w.hist = seg ? w.boxes + w.box_words : nullptr;
-  w.ctr = seg ? w.hist + segs * kBins : nullptr;
+  w.table = reinterpret_cast<uint32_t *>(p);
+  w.boxes = p ? w.table + slots : nullptr;
+  w.hist = p ? w.boxes + w.box_words : nullptr;
+  w.ctr = p ? w.hist + segs * kBins : nullptr;
+  w.count = p ? w.ctr + segs * 4 : nullptr;
+  w.dup = reinterpret_cast<uint8_t *>(p ? w.count + 1 : nullptr);
   return w;
 }
 
@@ -1426,7 +1547,7 @@ size_t sb_tree_bytes(int32_t fmt, int32_t channels, int32_t sw, int32_t sh) {
 size_t sb_tree_workspace_bytes(int32_t fmt, int32_t channels, int32_t sw, int32_t sh) {
   const int32_t t = search_texel_bytes(fmt, channels);
   if (t == 0 || !side_ok(sw) || !side_ok(sh)) return 0;
-  return build_ws(nullptr, size_t(sw) * size_t(sh), size_t(t), 0).total;
+  return build_ws(nullptr, size_t(sw) * size_t(sh), size_t(t)).total;
 }
 
 int sb_tree_build(const void *guide, int32_t fmt, int32_t channels, int32_t sw, int32_t sh,
@@ -1439,20 +1560,24 @@ int sb_tree_build(const void *guide, int32_t fmt, int32_t channels, int32_t sw, 
   const uint32_t n = uint32_t(sw) * uint32_t(sh);
   const TreeLayout l = tree_layout(n, size_t(t));
   if (tree_bytes < l.total) return SB_ENOMEM;
-  const BuildWs ws = build_ws(static_cast<char *>(workspace), n, size_t(t),
-                              2 * size_t(t) * 8 / size_t(fmt_depth(fmt)));
+  const BuildWs ws = build_ws(static_cast<char *>(workspace), n, size_t(t));
   if (workspace_bytes < ws.total) return SB_ENOMEM;
   char *tb = static_cast<char *>(tree);
   uint32_t *keys = reinterpret_cast<uint32_t *>(tb + l.keys);
   hipError_t e = with_format(fmt, t, [&](auto d, auto s) -> hipError_t {
     constexpr int D = decltype(d)::value, S = decltype(s)::value;
     const unsigned nblk = blocks_for(n, kSortBlock);
-    const uint64_t most = l.entries > ws.hist_words ? l.entries : ws.hist_words;
+    const uint32_t ones = ws.slots + ws.box_words;
+    const uint32_t most = l.entries > ones ? l.entries : ones;
     k_tree_clear<<<blocks_for(most, 256) < 2048 ? blocks_for(most, 256) : 2048, 256, 0, stream>>>(
-        keys, l.entries, ws.boxes, ws.box_words, ws.hist, ws.hist_words);
-    TexelsIn in = {guide, nullptr, n, uint32_t(sw)};
-    if (ws.splits > 0)
-      k_tree_box<D, S><<<nblk < 512 ? nblk : 512, 256, 0, stream>>>(guide, n, ws.boxes);
+        keys, l.entries, ws.table, ones, ws.hist, ws.zero_words);
+    MergeArgs m = {guide, n, uint32_t(sw), ws.table, ws.slots, {0u, 0u, 0u, 0u}, ws.dup};
+    for (int32_t k = 0; k < channels; ++k)
+      m.mask[k * D / 32] |= (D == 8 ? 0xFFu : 0xFFFFu) << (k * D % 32);
+    k_tree_merge<S><<<blocks_for(n, kMergeThreads), kMergeThreads, 0, stream>>>(m);
+    k_tree_take<D, S><<<blocks_for(n, 256 * kTakePer), 256, 0, stream>>>(
+        m, ws.vals[1], ws.keys[1], ws.count, ws.splits > 0 ? ws.boxes : nullptr);
+    TexelsIn in = {ws.vals[1], ws.keys[1], ws.count};
     for (int32_t lv = 0; lv < ws.splits; ++lv) {
       SplitArgs a;
       a.in = in;
@@ -1474,7 +1599,7 @@ int sb_tree_build(const void *guide, int32_t fmt, int32_t channels, int32_t sw, 
     }
     const SortArgs a = {in, tb + l.boxes, tb + l.vals, keys, l.levels, {wn[0], wn[1]}, channels};
     k_tree_sort<D, S><<<nblk, 512, 0, stream>>>(a);
-    k_tree_top<D, S><<<1, 1024, 0, stream>>>(tb + l.boxes, keys, l.levels, n,
+    k_tree_top<D, S><<<1, 1024, 0, stream>>>(tb + l.boxes, keys, l.levels, ws.count,
                                              reinterpret_cast<uint32_t *>(tb), uint32_t(channels));
     const hipError_t ec = hipGetLastError();
     if (ec != hipSuccess) return ec;
@@ -1497,15 +1622,15 @@ int sb_tree_query(const sb_style *style, const void *queries, int64_t n, uint32_
   uint32_t wn[2];
   if (t == 0 || !resolve_weights_n(style->weights, style->channels, wn)) return SB_EINVAL;
   if (n == 0) return SB_OK;
-  const TreeView tv = tree_view(style->tree, size_t(style->sw) * size_t(style->sh), size_t(t));
+  const TreeRef tree = tree_ref(style->tree, size_t(style->sw) * size_t(style->sh), size_t(t));
   hipError_t e = with_format(style->fmt, t, [&](auto d, auto s) -> hipError_t {
     constexpr int D = decltype(d)::value, S = decltype(s)::value;
     if (n <= kQueryWide)
-      k_tree_query<D, S, 8><<<blocks_for(uint64_t(n) * 8, 256), 256, stack_bytes<8>(tv.levels),
-                              stream>>>(tv, queries, uint32_t(n), out, wn[0], wn[1]);
+      k_tree_query<D, S, 8><<<blocks_for(uint64_t(n) * 8, 256), 256, stack_bytes<8>(tree.levels),
+                              stream>>>(tree, queries, uint32_t(n), out, wn[0], wn[1]);
     else
-      k_tree_query<D, S, 4><<<blocks_for(uint64_t(n) * 4, 256), 256, stack_bytes<4>(tv.levels),
-                              stream>>>(tv, queries, uint32_t(n), out, wn[0], wn[1]);
+      k_tree_query<D, S, 4><<<blocks_for(uint64_t(n) * 4, 256), 256, stack_bytes<4>(tree.levels),
+                              stream>>>(tree, queries, uint32_t(n), out, wn[0], wn[1]);
     return hipGetLastError();
   });
   if (e != hipSuccess) {
@@ -1521,12 +1646,11 @@ namespace sb {
 // The tree sections a frame of a search-format style reads.
 void fill_tree_args(const sb_style *style, FrameArgs *a) {
   const int32_t t = search_texel_bytes(style->fmt, style->channels);
-  const TreeView tv = tree_view(style->tree, size_t(style->sw) * size_t(style->sh), size_t(t));
-  a->t_boxes = tv.boxes;
-  a->t_vals = tv.vals;
-  a->t_last = tv.last;
-  a->t_keys = tv.keys;
-  a->t_levels = tv.levels;
+  const TreeRef tree = tree_ref(style->tree, size_t(style->sw) * size_t(style->sh), size_t(t));
+  a->t_boxes = tree.boxes;
+  a->t_vals = tree.vals;
+  a->t_keys = tree.keys;
+  a->t_levels = tree.levels;
   a->texel = t;
   resolve_weights_n(style->weights, style->channels, a->wn);
 }

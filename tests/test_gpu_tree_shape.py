@@ -1,0 +1,106 @@
+"""The search tree that a registration leaves in device memory: equal texels are one,
+every box and key that of the texels below it, so a guide of few values is as cheap
+to search as one of few texels.  Tolerance 0."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sb():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    import paper_1807_03249_amd as m
+
+    m.lib()
+    return m
+
+
+def _start(level):
+    return (8 ** level - 1) // 7
+
+
+def _up256(x):
+    return (x + 255) // 256 * 256
+
+
+def _guide(rng, depth, channels, sw, sh, spread):
+    top, dt = (1 << depth) - 1, np.uint8 if depth == 8 else np.uint16
+    elems = oracle.texel_bytes(depth, channels) * 8 // depth
+    y, x = np.mgrid[0:sh, 0:sw]
+    if spread == "noise":
+        g = rng.integers(0, top + 1, (sh, sw, elems))
+    elif spread == "one":
+        g = np.zeros((sh, sw, elems)) + rng.integers(0, top + 1, elems)
+    elif spread == "few":
+        g = rng.integers(0, top + 1, (5, elems))[rng.integers(0, 5, (sh, sw))]
+    elif spread == "steps":  # smooth, in eighths of the range
+        g = np.stack([(np.sin(x / (9 + k)) + np.cos(y / (7 + k)) + 2) * top / 4
+                      for k in range(elems)], -1) // (top // 8) * (top // 8)
+    else:  # "half": a constant left half beside noise
+        g = rng.integers(0, top + 1, (sh, sw, elems))
+        g[:, : sw // 2] = top // 3
+    g = np.ascontiguousarray(g.astype(dt))
+    g[..., channels:] = rng.integers(0, top + 1, g[..., channels:].shape)  # to be ignored
+    return g
+
+
+# fewer texels than a node, one more than a power of eight, one workgroup's merge
+# and more, one sort's block and more, and every kind of duplicates
+@pytest.mark.parametrize("depth,channels,sw,sh,spread", [
+    (8, 5, 1, 1, "one"), (8, 3, 5, 1, "few"), (16, 4, 13, 5, "noise"), (8, 2, 64, 48, "noise"),
+    (16, 7, 33, 31, "few"), (8, 5, 129, 127, "one"), (8, 5, 160, 150, "steps"),
+    (16, 4, 200, 90, "steps"), (8, 8, 150, 161, "half"), (16, 2, 100, 97, "half")])
+def test_tree_of_distinct_texels(sb, depth, channels, sw, sh, spread):
+    rng = np.random.default_rng(depth * 1000 + sw)
+    g = _guide(rng, depth, channels, sw, sh, spread)
+    n, t = sw * sh, g.shape[2] * depth // 8
+    print(f"[gpu-case] tree shape {depth}x{channels} {sw}x{sh} {spread}", flush=True)
+    st = sb.Style(np.zeros((sh, sw, 3), np.uint8), g, channels=channels)
+    raw = st.tree.cpu().numpy()
+    levels = 1
+    while 8 ** levels < n:
+        levels += 1
+    entries, m, texel, chans = (int(v) for v in raw[:16].view(np.uint32))
+
+    values, first = np.unique(g.reshape(n, -1)[:, :channels], axis=0, return_index=True)
+    assert m == len(values), "one texel per distinct value"
+    assert (entries, texel, chans) == (_start(levels) + m, t, channels)
+
+    padded = (n + 7) // 8 * 8
+    at_vals = 256 + _up256(_start(levels - 1) * 16 * t)
+    at_keys = at_vals + _up256(padded * t)
+    vals = raw[at_vals:at_vals + m * t].view(g.dtype).reshape(m, -1)[:, :channels].astype(np.int64)
+    keys = raw[at_keys:at_keys + (_start(levels) + padded) * 4].view(np.uint32)
+    boxes = raw[256:256 + _start(levels - 1) * 16 * t].view(g.dtype)
+    boxes = boxes.reshape(-1, 2, 8, g.shape[2])[..., :channels].astype(np.int64)
+
+    leaf = keys[_start(levels):]
+    assert np.all(leaf[m:] == 0xFFFFFFFF)
+    raster = (leaf[:m] >> 16).astype(np.int64) * sw + (leaf[:m] & 0xFFFF)
+    np.testing.assert_array_equal(np.sort(raster), np.sort(first))  # the first of its value
+    np.testing.assert_array_equal(vals, g.reshape(n, -1)[raster, :channels])
+    for level in range(levels - 1, 0, -1):
+        per = 8 ** (levels - level)
+        for p in range((m + per - 1) // per):
+            below = slice(p * per, min((p + 1) * per, m))
+            e = _start(level) + p
+            assert keys[e] == leaf[below].min()
+            box = boxes[(e - 1) >> 3, :, (e - 1) & 7]
+            np.testing.assert_array_equal(box[0], vals[below].min(0))
+            np.testing.assert_array_equal(box[1], vals[below].max(0))
+
+    # and the lookups, on values the guide holds and beside them
+    top = (1 << depth) - 1
+    q = g.reshape(n, -1)[rng.integers(0, n, 600)].astype(np.int64)
+    q[::2] = np.clip(q[::2] + rng.integers(-4, 5, q[::2].shape), 0, top)
+    q = np.ascontiguousarray(q.astype(g.dtype))
+    import torch
+
+    qt = torch.from_numpy(q.view(np.int16) if depth == 16 else q).cuda()
+    got = st.query(qt).cpu().numpy().view(np.uint32)
+    np.testing.assert_array_equal(got, oracle.nn_query_n(g, channels, q))
