@@ -104,3 +104,45 @@ def test_tree_of_distinct_texels(sb, depth, channels, sw, sh, spread):
     qt = torch.from_numpy(q.view(np.int16) if depth == 16 else q).cuda()
     got = st.query(qt).cpu().numpy().view(np.uint32)
     np.testing.assert_array_equal(got, oracle.nn_query_n(g, channels, q))
+
+
+def _leaves(vals, depth):
+    """The order that median splits leave the texels in: every run of 2^k texels
+    sorted along its widest element, texels at one value of it by the next widest
+    (its upper four bits of a 16-bit one's range), then by their index."""
+    at = np.arange(len(vals))
+    for lg in range(11, 3, -1):
+        for first in range(0, len(at), 1 << lg):
+            run = at[first:first + (1 << lg)]
+            ext = vals[run].max(0) - vals[run].min(0)
+            axis = int(ext.argmax())
+            ext[axis] = -1
+            near = int(ext.argmax())
+            low = vals[run, near].min()
+            shift = 0 if depth == 8 else max(int(vals[run, near].max() - low).bit_length() - 4, 0)
+            at[first:first + (1 << lg)] = run[np.lexsort((run, (vals[run, near] - low) >> shift,
+                                                          vals[run, axis]))]
+    return at
+
+
+# few values of every element, so that medians fall among texels they cannot tell
+# apart: without a second element these are split at random, and boxes overlap
+@pytest.mark.parametrize("depth,channels,steps", [(8, 3, 9), (8, 5, 3), (16, 4, 5), (16, 2, 30)])
+def test_equal_values_of_an_axis(sb, depth, channels, steps):
+    rng = np.random.default_rng(depth * 100 + channels)
+    elems = oracle.texel_bytes(depth, channels) * 8 // depth
+    values = np.stack(np.meshgrid(*[np.arange(steps)] * channels), -1).reshape(-1, channels)
+    values = values[rng.permutation(len(values))[:1000]] * (((1 << depth) - 1) // steps)
+    values[:, 1:] = values[:, 1:] * 3 // 4  # one element is the widest
+    n = len(values)
+    g = np.zeros((1, n, elems), np.uint8 if depth == 8 else np.uint16)
+    g[0, :, :channels] = values
+    print(f"[gpu-case] tree order {depth}x{channels} {n}", flush=True)
+    st = sb.Style(np.zeros((1, n, 3), np.uint8), g, channels=channels)
+    levels = 1
+    while 8 ** levels < n:
+        levels += 1
+    t = elems * depth // 8
+    at_keys = 256 + _up256(_start(levels - 1) * 16 * t) + _up256((n + 7) // 8 * 8 * t)
+    keys = st.tree.cpu().numpy()[at_keys:at_keys + (_start(levels) + n) * 4].view(np.uint32)
+    np.testing.assert_array_equal(keys[_start(levels):], _leaves(values.astype(np.int64), depth))
