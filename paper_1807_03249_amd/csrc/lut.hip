@@ -58,6 +58,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 struct LutWs {
   uint32_t *count;  // nb
   uint32_t *start;  // nb + 1
+  uint32_t *uneven; // 1 unless the pixels fill the buckets evenly (see k_lut_scan)
   uint2 *pts;       // npix: {g0 | g1 << 16, raster index}
   uint32_t *rank;   // npix: a pixel's rank in its bucket
   uint32_t *sums;   // the scan's block sums, in pts until the scatter fills it
@@ -70,7 +71,8 @@ LutWs lut_ws(void *base, const LutGeom &g) {
   w.count = reinterpret_cast<uint32_t *>(p);
   p += align256(nb * 4);
   w.start = reinterpret_cast<uint32_t *>(p);
-  p += align256((nb + 1) * 4);
+  w.uneven = w.start + nb + 1;
+  p += align256((nb + 2) * 4);
   w.pts = reinterpret_cast<uint2 *>(p);
   w.sums = reinterpret_cast<uint32_t *>(p);
   p += align256(size_t(g.npix) * 8);
@@ -301,8 +303,11 @@ __global__ void __launch_bounds__(256) k_lut_count(const void *guide, int32_t np
 // block adds up the sums before it (at most n / kScanBlock = 1024 of them)
 // and scans its own counts: 9 us for 2^20 buckets, launch bound (one
 // workgroup scanning all of them took 2.48 ms of the 2.73 ms a 2048 x 2048
-// style took).
+// style took).  The second also tells whether the pixels fill the buckets evenly:
+// none of them holds more than kFullBucket, and no block has more than half of
+// its own empty.
 constexpr uint32_t kScanPer = 16, kScanBlock = 256 * kScanPer;
+constexpr uint32_t kFullBucket = 32;
 // (dword-aligned: the workspace is the caller's)
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -315,8 +320,9 @@ __device__ inline uint32_t block_sum(uint32_t v, uint32_t *part) {  // 256 threa
 }
 
 __global__ void __launch_bounds__(256) k_lut_sums(const uint32_t *count, uint32_t n,
-                                                  uint32_t *sums) {
+                                                  uint32_t *sums, uint32_t *uneven) {
   __shared__ uint32_t part[4];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *uneven = 0u;
   uint32_t s = 0;
 #pragma unroll
   for (uint32_t k = 0; k < kScanPer / 4; ++k) {
@@ -331,8 +337,9 @@ __global__ void __launch_bounds__(256) k_lut_sums(const uint32_t *count, uint32_
 }
 
 __global__ void __launch_bounds__(256) k_lut_scan(const uint32_t *count, const uint32_t *sums,
-                                                  uint32_t n, uint32_t *start) {
-  __shared__ uint32_t part[4], wsum[4];
+                                                  uint32_t n, uint32_t *start,
+                                                  uint32_t *uneven) {
+  __shared__ uint32_t part[4], wsum[4], some[4];
   const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
   uint32_t before = 0;
   for (uint32_t b = t; b < blockIdx.x; b += 256) before += sums[b];
@@ -340,12 +347,14 @@ __global__ void __launch_bounds__(256) k_lut_scan(const uint32_t *count, const u
   // thread t owns counts [kScanPer t, kScanPer (t + 1)) of the block
   const uint32_t i0 = blockIdx.x * kScanBlock + kScanPer * t;
   u32x4a4 c[kScanPer / 4];
-  uint32_t s = 0;
+  uint32_t s = 0, held = 0, most = 0;
 #pragma unroll
   for (uint32_t k = 0; k < kScanPer / 4; ++k) {
     c[k] = u32x4a4{0u, 0u, 0u, 0u};
     if (i0 + 4 * k < n) c[k] = *reinterpret_cast<const u32x4a4 *>(count + i0 + 4 * k);
     s += c[k].x + c[k].y + c[k].z + c[k].w;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) held += c[k][j] != 0u, most = max(most, c[k][j]);
   }
   uint32_t incl = s;
 #pragma unroll
@@ -354,7 +363,10 @@ __global__ void __launch_bounds__(256) k_lut_scan(const uint32_t *count, const u
     if (lane >= o) incl += v;
   }
   if (lane == 63) wsum[wave] = incl;
-  __syncthreads();
+  // (block_sum's own words are still being read)
+  const uint32_t filled = block_sum(held, some);
+  const bool full = __any(most > kFullBucket);
+  if ((lane == 0 && full) || (t == 0 && 2 * filled < min(n, kScanBlock))) *uneven = 1u;
   uint32_t run = before + incl - s;
   for (uint32_t w = 0; w < wave; ++w) run += wsum[w];
 #pragma unroll
@@ -384,34 +396,18 @@ __global__ void __launch_bounds__(256) k_lut_scatter(const void *guide, int32_t 
   if (b != kNoBucket) pts[start[b] + rank[i]] = make_uint2(c0 | (c1 << 16), i);
 }
 
-// Q x Q bins of one bucket per thread (Q = 2 wherever buckets are at least two
-// bins wide, which is from two bits per channel on): one walk over the rings
-// of buckets serves them all, so every bucket's bounds and pixels are read a
-// quarter as often (4 M bins of a 2048 x 2048 style 15.6 us, 26 with one
-// bin per thread).  A candidate is distance << 26 | raster index (at most
-// 2^33 and 2^26), so ties go to the smallest index by themselves.
-// `fallback` (may be null): when no pixel was bucketed (a label absent from
-// the exemplar), copy this table instead.
+// Q x Q bins of one bucket, the first of them (cx, cy): one walk over the rings of
+// buckets serves them all, so every bucket's bounds and pixels are read once for Q x Q
+// bins.  A candidate is distance << 26 | raster index (at most 2^33 and 2^26), so ties
+// go to the smallest index by themselves.  Four pixels' loads are in flight together:
+// one after another, a long bucket (a guide of few values) takes as many round trips
+// as it has pixels (a 512 x 512 guide, half of it constant, at 9 bits 19 ms, 36 so).
 template <int Q>
-__global__ void __launch_bounds__(256) k_lut_query(const uint32_t *start, const uint2 *pts,
-                                                   int32_t lut_bits, int32_t bin_shift,
-                                                   int32_t bucket_bits, int32_t bucket_shift,
-                                                   int32_t sw, uint32_t *lut,
-                                                   const uint32_t *fallback) {
-  const uint32_t side = 1u << lut_bits, across = side / Q;
-  const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= across * across) return;
-  const uint32_t cx = t % across * Q, cy = t / across * Q;  // the first bin
-  if (fallback && start[1u << (2 * bucket_bits)] == 0) {
-#pragma unroll
-    for (int j = 0; j < Q; ++j)
-#pragma unroll
-      for (int i = 0; i < Q; ++i) {
-        const uint32_t c = (cy + j) * side + cx + i;
-        lut[c] = fallback[c];
-      }
-    return;
-  }
+__device__ __forceinline__ void lut_query(const uint32_t *start, const uint2 *pts, uint32_t cx,
+                                          uint32_t cy, int32_t lut_bits, int32_t bin_shift,
+                                          int32_t bucket_bits, int32_t bucket_shift, int32_t sw,
+                                          uint32_t *lut) {
+  const uint32_t side = 1u << lut_bits;
   const uint32_t half = bin_shift ? (1u << (bin_shift - 1)) : 0u;
   uint32_t qx[Q], qy[Q];
 #pragma unroll
@@ -425,6 +421,20 @@ __global__ void __launch_bounds__(256) k_lut_query(const uint32_t *start, const 
   for (int j = 0; j < Q; ++j)
 #pragma unroll
     for (int i = 0; i < Q; ++i) best[j][i] = ~0ull;
+  auto take = [&](const uint2 p) {
+    uint32_t dx[Q], dy[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const int32_t ex = int32_t(qx[i]) - int32_t(p.x & 0xFFFFu);
+      const int32_t ey = int32_t(qy[i]) - int32_t(p.x >> 16);
+      dx[i] = uint32_t(ex) * uint32_t(ex), dy[i] = uint32_t(ey) * uint32_t(ey);
+    }
+#pragma unroll
+    for (int j = 0; j < Q; ++j)
+#pragma unroll
+      for (int i = 0; i < Q; ++i)
+        best[j][i] = min(best[j][i], ((uint64_t(dx[i]) + dy[j]) << 26) | p.y);
+  };
   for (int32_t k = 0;; ++k) {
     const int32_t x0 = bx0 - k, x1 = bx0 + k, y0 = by0 - k, y1 = by0 + k;
     const int32_t ya = y0 > 0 ? y0 : 0, yb = y1 < nb - 1 ? y1 : nb - 1;
@@ -434,22 +444,13 @@ __global__ void __launch_bounds__(256) k_lut_query(const uint32_t *start, const 
       for (int32_t bx = x0; bx <= x1; bx += (step > 0 ? step : 1)) {
         if (bx < 0 || bx >= nb) continue;
         const uint32_t b = (uint32_t(by) << bucket_bits) | uint32_t(bx);
+        uint32_t e = start[b];
         const uint32_t e1 = start[b + 1];
-        for (uint32_t e = start[b]; e < e1; ++e) {
-          const uint2 p = pts[e];
-          uint32_t dx[Q], dy[Q];
-#pragma unroll
-          for (int i = 0; i < Q; ++i) {
-            const int32_t ex = int32_t(qx[i]) - int32_t(p.x & 0xFFFFu);
-            const int32_t ey = int32_t(qy[i]) - int32_t(p.x >> 16);
-            dx[i] = uint32_t(ex) * uint32_t(ex), dy[i] = uint32_t(ey) * uint32_t(ey);
-          }
-#pragma unroll
-          for (int j = 0; j < Q; ++j)
-#pragma unroll
-            for (int i = 0; i < Q; ++i)
-              best[j][i] = min(best[j][i], ((uint64_t(dx[i]) + dy[j]) << 26) | p.y);
+        for (; e + 4 <= e1; e += 4) {
+          const uint2 p0 = pts[e], p1 = pts[e + 1], p2 = pts[e + 2], p3 = pts[e + 3];
+          take(p0), take(p1), take(p2), take(p3);
         }
+        for (; e < e1; ++e) take(pts[e]);
       }
     }
     // distance from each centre to the nearest side of the searched box that
@@ -476,6 +477,35 @@ __global__ void __launch_bounds__(256) k_lut_query(const uint32_t *start, const 
       const uint32_t idx = uint32_t(best[j][i]) & 0x3FFFFFFu;
       lut[(cy + j) * side + cx + i] = pack_xy(idx % uint32_t(sw), idx / uint32_t(sw));
     }
+}
+
+// The table, a thread per bin or, where that pays, per 2 x 2 bins of one bucket
+// (buckets are at least two bins wide from two bits per channel on).  It pays on
+// evenly filled buckets (4 M bins of a 2048 x 2048 guide of texture coordinates
+// 15.6 us, 26 with one bin a thread): where the pixels crowd in a few, the walks
+// are long and a quarter of the threads waits too much for each (a 512 x 512
+// guide of constant regions at 9 bits 211 ms, 818 with 2 x 2 bins).
+// `fallback` (may be null): when no pixel was bucketed (a label absent from
+// the exemplar), copy this table instead.
+__global__ void __launch_bounds__(256) k_lut_query(const uint32_t *start, const uint32_t *uneven,
+                                                   const uint2 *pts, int32_t lut_bits,
+                                                   int32_t bin_shift, int32_t bucket_bits,
+                                                   int32_t bucket_shift, int32_t sw, uint32_t *lut,
+                                                   const uint32_t *fallback) {
+  const uint32_t t = blockIdx.x * 256 + threadIdx.x;
+  if (fallback && start[1u << (2 * bucket_bits)] == 0) {
+    if (t < 1u << (2 * lut_bits)) lut[t] = fallback[t];
+    return;
+  }
+  if (bucket_bits < lut_bits && *uneven == 0u) {
+    const uint32_t across = 1u << (lut_bits - 1);
+    if (t < across * across)
+      lut_query<2>(start, pts, t % across * 2, t / across * 2, lut_bits, bin_shift, bucket_bits,
+                   bucket_shift, sw, lut);
+  } else if (t < 1u << (2 * lut_bits)) {
+    lut_query<1>(start, pts, t & ((1u << lut_bits) - 1u), t >> lut_bits, lut_bits, bin_shift,
+                 bucket_bits, bucket_shift, sw, lut);
+  }
 }
 
 unsigned blocks_for(uint64_t n, unsigned bs) { return unsigned((n + bs - 1) / bs); }
@@ -506,7 +536,7 @@ size_t lut_workspace_bytes(int32_t fmt, int32_t sw, int32_t sh, int32_t lut_bits
   }
   LutGeom g = lut_geom(fmt, sw, sh, lut_bits);
   size_t nb = size_t(1) << (2 * g.bucket_bits);
-  return align256(nb * 4) + align256((nb + 1) * 4) + align256(size_t(g.npix) * 8) +
+  return align256(nb * 4) + align256((nb + 2) * 4) + align256(size_t(g.npix) * 8) +
          align256(size_t(g.npix) * 4);
 }
 
@@ -578,17 +608,14 @@ hipError_t build_one(const void *guide, int32_t fmt, int32_t sw, int32_t sh, int
   // the block sums (at most 1024 words, one per kScanBlock buckets) lie in
   // pts, which holds 8 bytes per pixel and at least one pixel per 4 buckets
   const unsigned sb = blocks_for(nb, kScanBlock);
-  k_lut_sums<<<sb, 256, 0, stream>>>(w.count, nb, w.sums);
-  k_lut_scan<<<sb, 256, 0, stream>>>(w.count, w.sums, nb, w.start);
+  k_lut_sums<<<sb, 256, 0, stream>>>(w.count, nb, w.sums, w.uneven);
+  k_lut_scan<<<sb, 256, 0, stream>>>(w.count, w.sums, nb, w.start, w.uneven);
   k_lut_scatter<<<blocks_for(g.npix, 256), 256, 0, stream>>>(
       guide, g.npix, shift, g.bucket_bits, w.start, w.rank, w.pts, labels, want);
   const uint64_t nbins = uint64_t(1) << (2 * lut_bits);
-  if (g.bucket_bits < lut_bits)
-    k_lut_query<2><<<blocks_for(nbins / 4, 256), 256, 0, stream>>>(
-        w.start, w.pts, lut_bits, g.depth - lut_bits, g.bucket_bits, shift, sw, lut, fallback);
-  else
-    k_lut_query<1><<<blocks_for(nbins, 256), 256, 0, stream>>>(
-        w.start, w.pts, lut_bits, g.depth - lut_bits, g.bucket_bits, shift, sw, lut, fallback);
+  k_lut_query<<<blocks_for(nbins, 256), 256, 0, stream>>>(
+      w.start, w.uneven, w.pts, lut_bits, g.depth - lut_bits, g.bucket_bits, shift, sw, lut,
+      fallback);
   return hipGetLastError();
 }
 }  // namespace
