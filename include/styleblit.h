@@ -356,22 +356,24 @@ size_t sb_noalloc_scratch_bytes(void);
  * differ only in speed, so an autotuner may pick any.  0 in a field takes the
  * library's default.
  *   blend_ppt    pixels per thread of the voting pass, adjacent in a row: 2 or
- *                4 (default 4, frames of up to 2^18 pixels 2); each vote
+ *                4 (default 4, frames of up to 2^17 pixels 2); each vote
  *                gather loads that many texels
- *   blend_rows   rows of the voting tile: 8 or 16 (default 8, in batches 16);
+ *   blend_rows   rows of the voting tile: 8 or 16 (default 16, frames of up to
+ *                2^17 pixels 8);
  *                the tile is (16 * blend_ppt) x blend_rows pixels, one thread
  *                per blend_ppt pixels
  *   level_group  levels of Algorithm 2 whose source-guide gathers are in
  *                flight together before their tests: 2 or 4 (default 2)
  *   level_ppt    pixels per thread of the level loop, i.e. 8x8 blocks per
  *                wave: 1, 2 (side by side) or 4 (2 x 2) (default 2, frames of
- *                up to 2^19 pixels 1; in batches always 2); the blocks of a
+ *                up to 2^19 pixels 1; in batches 2); the blocks of a
  *                wave share the seed records they have in common
  *   blend_split  2: the voting pass copies the texel of every pixel group
  *                whose whole window holds one offset (their exact average)
  *                and votes the other groups from a per-tile list; 1: every
- *                group votes in place (default 1; large frames with a
- *                threshold that makes large chunks 2, with 16 rows) */
+ *                group votes in place (default 1; 2 for frames above
+ *                2^21 pixels with a threshold that makes large chunks, and
+ *                above 2^18 from radius 6 on; in batches 1) */
 typedef struct {
     int32_t blend_ppt;
     int32_t blend_rows;

@@ -151,15 +151,19 @@ bool resolve_weights(int32_t fmt, const uint8_t *in, int32_t out[3]) {
 }
 
 // Small frames leave the chip (1024 SIMDs) short of waves, so they take fewer
-// pixels per thread although that costs more instructions: at 256 x 256 a
-// normal-guided frame of radius 2 takes 9.0 us with 2 and 1 pixels per thread
-// (vote, level loop), 9.8 with 4 and 1 and 12.3 with the 64 x 16 voting tiles
-// and 2; at 400 x 300 and radius 3 11.8, 12.9 and 15.0.  The vote's line lies
-// where 32 x 8 tiles give every SIMD two waves: 640 x 400 takes 14.8 and 14.3
-// us at radius 3 (23.8 and 24.7 at radius 6), 640 x 480 17.8 and 15.4.  The
-// level loop's: 900 x 600 takes 21.4 us with 1 and 21.6 with 2, 1280 x 720
-// 29.4 and 28.7.  Tiles of 8 rows cost halo but fit the chip more evenly
-// (1080p 43.4 us, 46.3 with 16 rows).
+// pixels per thread and smaller tiles although that costs more instructions and
+// texels read: at 400 x 300 2 pixels per thread, 8 rows and one block per wave take
+// 0.74 to 0.93 of the time of 4, 16 and two, at 512 x 384 0.82 to 1.31.  The line
+// of 2^17 lies between, where every SIMD has a wave of 32 x 8 tiles.  The level
+// loop's: 800 x 600 takes 0.96 of that time with one block per wave and 0.96 with
+// two, 640 x 480 0.92 and 0.95, 1280 x 720 0.99 and 0.97.
+//
+// Tiles have 16 rows from there on.  8 rows read each exemplar texel from L2 for
+// 14 rows of windows a tile, 16 rows for 22: where neighbouring pixels come from
+// all over the exemplar (a 1080p frame with folded texture coordinates 100 us
+// against 78, on noise likewise) the vote is bound by that.  Where they come from
+// one place 8 rows fit the chip more evenly (a 1080p normal-guided frame alone
+// 44.6 us against 45.8, but 37.2 against 36.0 with a second frame beside it).
 //
 // Copying uniform windows pays for its flags where most windows are uniform:
 // chunks are large when the threshold admits a step of two texels of a 16-bit
@@ -167,17 +171,20 @@ bool resolve_weights(int32_t fmt, const uint8_t *in, int32_t out[3]) {
 // place 107; 16384 89 and 102; 1024, one texel, 125 and 120) or an eighth of
 // the range of 8-bit channels (4K normals: t = 1024 98.9 and 101.1, 256 113
 // and 108; three channels 8192 95 and 102, 2048 121 and 116), and it pays on
-// large frames only (1080p at t = 4096 38.7 and 38.6, at 1024 and 512 x 512
-// texture coordinates 49 and 45).  It has less to gain from small tiles.
+// large frames only (voting in place takes 1.09 of its time at 4K, 1.05 at
+// 2560 x 1440, 1.02 and less at 1080p).  From radius 6 on a group costs so many
+// gathers that finding the few uniform ones pays at any threshold (radius 7, in
+// place: 1.07 at 1024 x 700, 1.04 at 4K; radius 5 1.00).
 Tune frame_tune(const FrameArgs &a) {
   const int64_t px = int64_t(a.w) * a.h;
+  if (px <= 1 << 17) return Tune{2, 8, 2, 1, 1};
   const uint64_t side = uint64_t(a.sw > a.sh ? a.sw : a.sh);
   const bool tolerant = a.fmt == SB_GUIDE_U16X2   ? a.threshold * side * side >= uint64_t(1) << 34
                         : a.fmt == SB_GUIDE_U8X2 ? a.threshold >= 1024
                         : a.fmt == SB_GUIDE_U8X3 ? a.threshold >= 4096
                                                  : false;
-  if (tolerant && px >= 3 << 20) return Tune{4, 16, 2, 2, 2};
-  return Tune{px <= 1 << 18 ? 2 : 4, 8, 2, px <= 1 << 19 ? 1 : 2, 1};
+  const bool split = (tolerant && px > 1 << 21) || (a.radius >= 6 && px > 1 << 18);
+  return Tune{4, 16, 2, px <= 1 << 19 ? 1 : 2, split ? 2 : 1};
 }
 
 // A batch fills the chip: large tiles for the least halo (64 frames of 0.3 to

@@ -1,0 +1,100 @@
+"""The default kernel choice of a frame: its outputs on both sides of each of its
+lines equal an explicit choice's (tolerance 0), and where neighbouring pixels take
+their texels from all over the exemplar it costs no more than an explicit choice."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sb():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    import paper_1807_03249_amd as m
+
+    m.lib()
+    return m
+
+
+def _folded(size, k, top):
+    """Smooth channels that meet every value in many places."""
+    import torch
+
+    y, x = torch.meshgrid(*[torch.arange(size, device="cuda")] * 2, indexing="ij")
+    v = [(torch.sin(x / (37.0 + 9 * c)) + torch.cos(y / (31.0 + 7 * c)) + 2) * top / 4 for c in range(k)]
+    return torch.stack(v, -1).to(torch.int32)
+
+
+def _as(fmt, v):
+    import torch
+
+    return (v.to(torch.int16) if fmt == "u16x2" else v.to(torch.uint8)).contiguous()
+
+
+def _style(sb, fmt, size, bits):
+    import torch
+
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(size)
+    g = _folded(size, 4 if fmt == "u8x3" else 2, 65535 if fmt == "u16x2" else 255)
+    rgb = (torch.rand(size, size, 3, generator=gen, device="cuda") * 255).to(torch.uint8)
+    return sb.Style(rgb, _as(fmt, g), bits)
+
+
+# 2^17 and 2^18 pixels about the radius from which uniform windows are copied, and
+# 2^21 pixels about the thresholds that do
+@pytest.mark.parametrize("fmt,w,h,threshold,radius", [
+    ("u8x2", 512, 256, 32, 3), ("u16x2", 513, 256, 4096, 7), ("u8x3", 512, 512, 192, 6),
+    ("u8x2", 513, 512, 32, 5), ("u8x2", 513, 512, 32, 6), ("u16x2", 1025, 512, 4096, 7),
+    ("u8x2", 2048, 1024, 1024, 2), ("u8x2", 2049, 1024, 1024, 2), ("u8x2", 2049, 1024, 1023, 2),
+    ("u16x2", 2049, 1024, 1 << 20, 1), ("u16x2", 2049, 1024, (1 << 20) - 1, 1),
+    ("u8x3", 2049, 1024, 4096, 3)])
+def test_lines_of_the_default(sb, fmt, w, h, threshold, radius):
+    import torch
+
+    st = _style(sb, fmt, 128, 7)
+    k, top = (4 if fmt == "u8x3" else 2), (65535 if fmt == "u16x2" else 255)
+    tgt = _as(fmt, _folded(max(w, h), k, top)[:h, :w] + torch.arange(w, device="cuda")[None, :, None] % 3)
+    p = sb.params(4, 8, threshold, radius, seed=w)
+    print(f"[gpu-case] default line {fmt} {w}x{h} t={threshold} r={radius}", flush=True)
+    got = sb.stylize(st, tgt, None, p, want_nnf=True)
+    for tune in ((4, 8, 4, 4, 1), (2, 16, 2, 1, 2)):
+        want = sb.stylize(st, tgt, None, p, want_nnf=True, tune=tune)
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+
+
+# texture coordinates that jump over the exemplar (8 rows a tile took 1.28 times 16
+# rows there), and noise, at few pixels (2 pixels a thread took 1.4 times 4)
+@pytest.mark.parametrize("w,h,noise,radius,tune", [(1920, 1080, False, 3, (4, 16, 2, 2, 1)),
+                                                   (600, 400, True, 7, (4, 16, 2, 1, 1))])
+def test_scattered_texels_cost(sb, w, h, noise, radius, tune):
+    import torch
+
+    st = _style(sb, "u16x2", 512, 9)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(w)
+    if noise:
+        tgt = torch.randint(0, 65536, (h, w, 2), generator=gen, device="cuda")
+    else:
+        y, x = torch.meshgrid(torch.arange(h, device="cuda"), torch.arange(w, device="cuda"), indexing="ij")
+        tgt = torch.stack([(x + 8 * torch.sin(y / 40)) % 512, (y + 8 * torch.cos(x / 40)) % 512], -1) * 128
+    tgt = _as("u16x2", tgt.to(torch.int32))
+    p = sb.params(4, 8, 4096, radius, seed=1)
+    out = (torch.empty(h, w, 3, dtype=torch.uint8, device="cuda"),
+           torch.empty(h, w, dtype=torch.int32, device="cuda"),
+           torch.empty(sb.workspace_bytes(w, h, p), dtype=torch.uint8, device="cuda"))
+    plans = [sb.FramePlan(st, tgt, None, p, *out, tune=t) for t in (None, tune)]
+    best = [float("inf")] * 2
+    print(f"[gpu-case] scattered texels {w}x{h}", flush=True)
+    for _ in range(7):
+        for i, plan in enumerate(plans):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            for _ in range(10):
+                plan.launch()
+            t[1].record()
+            t[1].synchronize()
+            best[i] = min(best[i], t[0].elapsed_time(t[1]))
+    assert best[0] < 1.12 * best[1]
