@@ -1435,6 +1435,8 @@ __global__ void __launch_bounds__(256) k_tree_query(TreeRef tree, const void *q,
 // 69 with four lanes, 90 with two), four more searches per instruction beyond.
 constexpr int kFallbackLanes = 2;
 constexpr int64_t kQueryWide = 65536;
+// Queries of one launch: a grid has fewer than 2^32 threads.
+constexpr int64_t kQueryLaunch = int64_t(1) << 29;
 // Workgroups of the fallback pass: what the chip holds.
 constexpr unsigned kFallbackGrid = 2048;
 
@@ -1642,12 +1644,18 @@ int sb_tree_query(const sb_style *style, const void *queries, int64_t n, uint32_
   const TreeRef tree = tree_ref(style->tree, size_t(style->sw) * size_t(style->sh), size_t(t));
   hipError_t e = with_format(style->fmt, t, [&](auto d, auto s) -> hipError_t {
     constexpr int D = decltype(d)::value, S = decltype(s)::value;
-    if (n <= kQueryWide)
-      k_tree_query<D, S, 8><<<blocks_for(uint64_t(n) * 8, 256), 256, stack_bytes<8>(tree.levels),
-                              stream>>>(tree, queries, uint32_t(n), out, wn[0], wn[1]);
-    else
-      k_tree_query<D, S, 4><<<blocks_for(uint64_t(n) * 4, 256), 256, stack_bytes<4>(tree.levels),
-                              stream>>>(tree, queries, uint32_t(n), out, wn[0], wn[1]);
+    for (int64_t at = 0; at < n; at += kQueryLaunch) {
+      const uint32_t m = uint32_t(n - at < kQueryLaunch ? n - at : kQueryLaunch);
+      const void *q = static_cast<const char *>(queries) + at * S;
+      if (n <= kQueryWide)
+        k_tree_query<D, S, 8><<<blocks_for(uint64_t(m) * 8, 256), 256,
+                                stack_bytes<8>(tree.levels), stream>>>(tree, q, m, out + at,
+                                                                       wn[0], wn[1]);
+      else
+        k_tree_query<D, S, 4><<<blocks_for(uint64_t(m) * 4, 256), 256,
+                                stack_bytes<4>(tree.levels), stream>>>(tree, q, m, out + at,
+                                                                       wn[0], wn[1]);
+    }
     return hipGetLastError();
   });
   if (e != hipSuccess) {
