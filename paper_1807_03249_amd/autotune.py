@@ -19,13 +19,15 @@ from typing import Dict, Iterable, List, Optional, Sequence, Tuple
 from . import TUNES, Batch, FrameJob, SbParams, Style, _torch, stylize
 
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "styleblit_gfx950", "tune.json")
-BATCH_BLOCKS_PER_CU = (2, 4, 8, 16)
+# 0: the library's default, which launches batches too small for a graph directly
+# (two frames 46 us, 61 as a graph); any other value replays the graph
+BATCH_BLOCKS_PER_CU = (0, 2, 4, 8, 16)
 
 
 def _device_name(torch) -> str:
     # the tag changes whenever the set of kernel choices does, so cached
     # winners of an older set are never read back
-    return torch.cuda.get_device_name(0) + "|choices5"
+    return torch.cuda.get_device_name(0) + "|choices6"
 
 
 def _load(path: str) -> Dict[str, dict]:
@@ -124,8 +126,8 @@ def tune_batch(jobs: List[FrameJob], candidates: Iterable[Tuple] = TUNES,
                blocks_per_cu: Iterable[int] = BATCH_BLOCKS_PER_CU, reps: int = 3,
                cache_path: Optional[str] = DEFAULT_CACHE, refresh: bool = False,
                workspace=None) -> dict:
-    """Fastest bit-exact (tune, blocks_per_cu) for graph-captured batches of
-    this shape mix.  The reference outputs are the default choice's, run as
+    """Fastest bit-exact (tune, blocks_per_cu) for batch plans on this shape
+    mix.  The reference outputs are the default choice's, run as
     separate frames.  Returns {"tune", "blocks_per_cu", "ms", "candidates",
     "cached"}."""
     torch = _torch()
