@@ -1014,10 +1014,10 @@ __global__ void __launch_bounds__(256) k_batch_seeds(const unsigned char *__rest
   });
 }
 
-// The default choices are scheduled for the waves per SIMD that their registers
-// allow anyway (72, three values in scratch, and 80): 64 frames 1019 us as a
-// graph and 1028 launched directly, 1040 and 1053 without the hint (with one
-// wave more each 1006 directly, but 1084 as a graph).
+// The default choice is scheduled for the seven waves per SIMD that 72 registers
+// allow (three values in scratch): 64 frames 1019 us as a graph and 1028 launched
+// directly, 1038 and 1053 without the hint (batches of 16 to 48 frames 0.98 to 1.00
+// of the time without, of two 1.02).  The vote gains nothing from one.
 template <int G, int B>
 __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(G == 2 && B == 2 ? 7 : 1)))
@@ -1040,7 +1040,6 @@ __global__ void __launch_bounds__(256)
 
 template <int PPT, int TH, int RLO, int RHI, bool SPLIT>
 __global__ void __launch_bounds__(16 * TH)
-    __attribute__((amdgpu_waves_per_eu(RLO == 0 && !SPLIT ? 6 : 1)))
     k_batch_blend(const unsigned char *__restrict__ desc) {
   constexpr int WORDS = blend_tile_words(PPT, TH, RHI, SPLIT);
   batch_loop<RLO == 0 ? 2 : 3, 16 * TH, WORDS>(desc, [](const FrameArgs &fa, uint32_t local,
