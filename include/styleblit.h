@@ -481,18 +481,19 @@ size_t sb_batch_workspace_bytes(const sb_frame *frames, int32_t n);
  * per-pixel level loop, voting for radius 0..3 and for 4..7) that stride
  * over the concatenated tiles of all frames of the batch.  The graphs hold
  * no shapes, so they serve every later batch; with the default grid, batches
- * too small for it are launched directly.  With use_graph == 0 each run
+ * too small for it (frames of table formats below 6144 pixels per block of the
+ * grid, 25 Mpixel in all on 256 compute units) are launched directly.  With use_graph == 0 each run
  * enqueues the upload and the same kernels directly, each with an exact
  * grid (one workgroup per tile of the batch, no persistent loop), so batches
  * on several streams interleave on the device as separate frames would.
  * tune (may be NULL) fixes the kernel choice of every run; blocks_per_cu
- * (0 = 16, else 1..16) sets the persistent grid of the graphs to that many
- * blocks per compute unit. */
+ * 1..16 sets the persistent grid of the graphs to that many blocks per compute
+ * unit, and every batch replays them; 0 is the default, 16. */
 int sb_batch_create(void *desc_dev, void *desc_host, int32_t use_graph, const sb_tune *tune,
                     int32_t blocks_per_cu, hipStream_t stream, sb_batch **out);
 /* Stylise n frames (1..sb_batch_max_frames()) with one graph launch (or the
- * launches it stands for) on `stream` (frames of many-channel styles follow it through the per-frame
- * kernels); the results equal n separate sb_stylize calls bit for bit.
+ * launches it stands for) on `stream` (frames of many-channel styles follow it
+ * through the per-frame kernels); the results equal n separate sb_stylize calls bit for bit.
  * Validates every frame first (SB_EINVAL / SB_ENOMEM and nothing enqueued
  * on a bad argument).  Blocks only while the run two calls back still reads
  * the descriptor half this run reuses.  workspace [device] of at least

@@ -694,10 +694,12 @@ def stylize_frames(jobs, workspace=None, tune=None):
 
 
 class Batch:
-    """A batch plan: many frames per launch.  With ``use_graph`` the launch
-    is one replay of a hipGraph captured once (descriptor upload + the
-    persistent kernels) on the plan's own stream.  ``tune`` and
-    ``blocks_per_cu`` fix the kernel choice and persistent grid."""
+    """A batch plan: many frames per launch.  With ``use_graph`` a batch is
+    one replay of a hipGraph captured once (descriptor upload + the
+    persistent kernels) on the plan's own stream, or, with the default grid
+    (``blocks_per_cu`` 0) and too few pixels for it, the same work launched
+    directly.  ``tune`` and ``blocks_per_cu`` fix the kernel choice and
+    persistent grid; with a grid given every batch replays the graph."""
 
     def __init__(self, use_graph: bool = True, tune=None, blocks_per_cu: int = 0):
         torch = _torch()

@@ -35,7 +35,8 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Default workgroups per compute unit of the persistent grids: twice what a
 // unit holds, so that one with cheap tiles takes more of them (64 frames
-// 1060 us, with 12 1079 and with 8 1137).
+// 1060 us, with 12 1079 and with 8 1137, before their kernels were scheduled for
+// their waves: 1019).
 constexpr uint32_t kBlocksPerCu = 16;
 // Pixels per workgroup of that grid from which a graph is replayed.
 constexpr uint64_t kGraphPixels = 6144;
@@ -63,6 +64,21 @@ hipError_t upload(const sb_batch *b, int k, int32_t n, hipStream_t stream) {
       reinterpret_cast<const uint64_t *>(b->desc_host[k]),
       reinterpret_cast<uint64_t *>(b->desc_dev[k]), words);
   return hipGetLastError();
+}
+
+// Whether a run replays the plan's graph.  Its persistent grid is the same
+// whatever the batch: the uneven shares even out over several tiles per workgroup,
+// and below that direct launches are faster (64 frames, 45 Mpixel: 1019 us and 1028
+// launched directly; 16 frames 302 and 285, two 60.8 and 45.7) unless the caller
+// chose the grid.  Frames of the search formats run after either, so they don't
+// count.
+bool replays_graph(const sb_batch *b, const sb_frame *frames, int32_t n) {
+  if (!b->use_graph || b->grid_given) return b->use_graph;
+  uint64_t px = 0;
+  for (int32_t f = 0; f < n; ++f)
+    if (frames[f].style && !fmt_search(frames[f].style->fmt))
+      px += uint64_t(frames[f].w) * uint64_t(frames[f].h);
+  return px >= uint64_t(b->grid) * kGraphPixels;
 }
 
 hipError_t batch_cleanup(sb_batch *b) {
@@ -164,14 +180,7 @@ int sb_batch_run(sb_batch *b, const sb_frame *frames, int32_t n, void *workspace
   // the search formats (many-channel guides) to the per-frame kernels after
   // them on the same stream (search[0 .. ns)), each in its own workspace
   static thread_local FrameArgs args[kMaxBatchFrames], search[kMaxBatchFrames];
-  // a plan's graph replays its persistent grid whatever the batch: the uneven
-  // shares even out over several tiles per workgroup, and below that direct
-  // launches are faster (64 frames, 45 Mpixel: 1019 us and 1028 launched
-  // directly; 16 frames 302 and 285, two 60.8 and 45.7) unless the caller chose
-  // the grid
-  uint64_t px = 0;
-  for (int32_t f = 0; f < n; ++f) px += uint64_t(frames[f].w) * uint64_t(frames[f].h);
-  const bool graph = b->use_graph && (b->grid_given || px >= uint64_t(b->grid) * kGraphPixels);
+  const bool graph = replays_graph(b, frames, n);
   char *ws = static_cast<char *>(workspace);
   int32_t nt = 0, ns = 0;
   for (int32_t f = 0; f < n; ++f) {
