@@ -482,7 +482,8 @@ size_t sb_batch_workspace_bytes(const sb_frame *frames, int32_t n);
  * over the concatenated tiles of all frames of the batch.  The graphs hold
  * no shapes, so they serve every later batch; with the default grid, batches
  * too small for it (frames of table formats below 6144 pixels per block of the
- * grid, 25 Mpixel in all on 256 compute units) are launched directly.  With use_graph == 0 each run
+ * grid, 25 Mpixel in all on 256 compute units) are launched directly, unless
+ * their stream is being captured.  With use_graph == 0 each run
  * enqueues the upload and the same kernels directly, each with an exact
  * grid (one workgroup per tile of the batch, no persistent loop), so batches
  * on several streams interleave on the device as separate frames would.

@@ -71,14 +71,19 @@ hipError_t upload(const sb_batch *b, int k, int32_t n, hipStream_t stream) {
 // and below that direct launches are faster (64 frames, 45 Mpixel: 1019 us and 1028
 // launched directly; 16 frames 302 and 285, two 60.8 and 45.7) unless the caller
 // chose the grid.  Frames of the search formats run after either, so they don't
-// count.
-bool replays_graph(const sb_batch *b, const sb_frame *frames, int32_t n) {
+// count.  A stream that is being captured would record direct launches, with a
+// descriptor half that later runs fill again: there a plan with graphs runs its
+// graph at once, whatever the batch.
+bool replays_graph(const sb_batch *b, const sb_frame *frames, int32_t n, hipStream_t stream) {
   if (!b->use_graph || b->grid_given) return b->use_graph;
   uint64_t px = 0;
   for (int32_t f = 0; f < n; ++f)
     if (frames[f].style && !fmt_search(frames[f].style->fmt))
       px += uint64_t(frames[f].w) * uint64_t(frames[f].h);
-  return px >= uint64_t(b->grid) * kGraphPixels;
+  if (px >= uint64_t(b->grid) * kGraphPixels) return true;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (stream && hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
+  return st != hipStreamCaptureStatusNone;
 }
 
 hipError_t batch_cleanup(sb_batch *b) {
@@ -180,7 +185,7 @@ int sb_batch_run(sb_batch *b, const sb_frame *frames, int32_t n, void *workspace
   // the search formats (many-channel guides) to the per-frame kernels after
   // them on the same stream (search[0 .. ns)), each in its own workspace
   static thread_local FrameArgs args[kMaxBatchFrames], search[kMaxBatchFrames];
-  const bool graph = replays_graph(b, frames, n);
+  const bool graph = replays_graph(b, frames, n, stream);
   char *ws = static_cast<char *>(workspace);
   int32_t nt = 0, ns = 0;
   for (int32_t f = 0; f < n; ++f) {
