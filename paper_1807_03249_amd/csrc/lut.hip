@@ -84,16 +84,21 @@ LutWs lut_ws(void *base, const LutGeom &g) {
 
 constexpr uint64_t kNoKey = ~0ull;
 constexpr int32_t kSepTile = 16;  // columns of one pass block
+constexpr int32_t kManyLabels = 8;
 
 // f0[value tuple c0 | c1 << 8 (| c2 << 16)] = smallest raster index holding
 // it (pre-filled with ~0u); with `labels`, only pixels labelled `want`.  Only
 // pixels that may lower an entry take an atomic: not one whose left neighbour
 // holds the same value, nor one that already finds a smaller index (a stale
 // value of a falling entry only costs an atomic): 512 x 512 normals of a
-// sphere, most of them one of few values, 3 us (8.4 with one per pixel).
+// sphere, most of them one of few values, 3 us (8.4 with one per pixel).  Where
+// more than kManyLabels labels share the pixels (`check` 0) few of a pass's pixels
+// are its own and waiting for the entry costs more: 16 tables of 2048 x 2048 noise
+// 527 us, 980 with it.
 template <int FMT>
 __global__ void __launch_bounds__(256) k_sep_sites(const void *guide, int32_t npix, uint32_t *f0,
-                                                   const uint8_t *labels, int32_t want) {
+                                                   const uint8_t *labels, int32_t want,
+                                                   int32_t check) {
   const uint32_t i = blockIdx.x * 256 + threadIdx.x;
   uint32_t v = ~0u;  // no value
   if (i < uint32_t(npix) && (!labels || labels[i] == want))
@@ -101,7 +106,7 @@ __global__ void __launch_bounds__(256) k_sep_sites(const void *guide, int32_t np
                              : static_cast<const uint32_t *>(guide)[i] & 0xFFFFFFu;
   const uint32_t left = uint32_t(__shfl_up(int(v), 1, 64));  // every lane takes part
   if (v == ~0u || ((threadIdx.x & 63u) != 0 && v == left)) return;
-  if (f0[v] > i) atomicMin(&f0[v], i);
+  if (!check || f0[v] > i) atomicMin(&f0[v], i);
 }
 
 // One channel of the minimisation.  The input is [outer][256][inner]: keys,
@@ -124,6 +129,11 @@ __global__ void __launch_bounds__(256) k_sep_sites(const void *guide, int32_t np
 // 512 x 512 three-channel exemplar's 2^24 bins take 134, 133 and 165 us (138,
 // 608 and 901 with every bin searched over the whole list); a two-channel
 // one's two passes 7 and 9 us (13.4 and 13.7), there the longest thread.
+//
+// A short list is searched whole for every bin (up to kShortWork candidates a
+// thread): the turns from bin to bin would take longer (16 tables of a 64 x 64
+// guide with labels 272 us, 234 so).
+constexpr int32_t kShortWork = 128;
 constexpr uint64_t kFarKey = 0x70000000FFFFFFFFull;  // staged for "no key": beyond every distance
 
 template <bool SITES, bool FINAL>
@@ -197,6 +207,23 @@ __global__ __launch_bounds__(256) void k_sep_pass(const void *in, uint64_t *out,
       out[dst] = none ? kNoKey : best;
     }
   };
+  if (nb * count <= kShortWork * slots) {
+    for (int32_t b = slot; b < nb; b += slots) {
+      const int32_t centre = (b << sft) + half;
+      best = kNoKey, best_at = 0;
+      for (int32_t n = 0; n < count; n += 4) {
+        const uint32_t v4 = *reinterpret_cast<const uint32_t *>(vlist + n);
+        uint64_t k[4];
+#pragma unroll
+        for (int32_t m = 0; m < 4; ++m)
+          k[m] = key[int32_t((v4 >> (8 * m)) & 0xFFu) * kSepTile + j];
+#pragma unroll
+        for (int32_t m = 0; m < 4; ++m) weigh(centre, int32_t((v4 >> (8 * m)) & 0xFFu), 0, k[m]);
+      }
+      emit(b);
+    }
+    return;
+  }
   // the first bins, a quarter of the list per thread
   const int32_t firsts = slots / 4, part = slot & 3;
   int32_t step = nb > firsts ? nb / firsts : 1;
@@ -559,21 +586,23 @@ void sep_pass(const void *in, uint64_t *out, uint32_t *lut, const uint32_t *fall
 
 hipError_t build_sep(const void *guide, int32_t fmt, int32_t sw, int32_t sh, int32_t lut_bits,
                      const int32_t *wt, uint32_t *lut, void *workspace, const uint8_t *labels,
-                     int32_t want, const uint32_t *fallback, hipStream_t stream) {
+                     int32_t want, int32_t nlabels, const uint32_t *fallback,
+                     hipStream_t stream) {
   const int32_t nch = fmt_channels(fmt);
   const int32_t nb = 1 << lut_bits, npix = sw * sh;
   uint64_t *x = static_cast<uint64_t *>(workspace);
   char *y = static_cast<char *>(workspace) + sep_x_bytes(nch, lut_bits);
   uint32_t *f0 = reinterpret_cast<uint32_t *>(y);
   const uint32_t nsites = 1u << (8 * nch);
+  const int32_t check = nlabels <= kManyLabels;
   k_fill_u32<<<blocks_for(nsites, 256) < 4096 ? blocks_for(nsites, 256) : 4096, 256, 0, stream>>>(
       f0, nsites, ~0u);
   if (fmt == SB_GUIDE_U8X2)
     k_sep_sites<SB_GUIDE_U8X2><<<blocks_for(npix, 256), 256, 0, stream>>>(guide, npix, f0, labels,
-                                                                          want);
+                                                                          want, check);
   else
     k_sep_sites<SB_GUIDE_U8X3><<<blocks_for(npix, 256), 256, 0, stream>>>(guide, npix, f0, labels,
-                                                                          want);
+                                                                          want, check);
   // channel 0: [v_rest][v0] -> [v_rest][b0]
   sep_pass<true, false>(f0, x, nullptr, nullptr, size_t(1) << (8 * (nch - 1)), 1, lut_bits,
                         wt[0], sw, stream);
@@ -593,10 +622,11 @@ hipError_t build_sep(const void *guide, int32_t fmt, int32_t sw, int32_t sh, int
 // One table: over all source pixels (labels null) or those labelled `want`.
 hipError_t build_one(const void *guide, int32_t fmt, int32_t sw, int32_t sh, int32_t lut_bits,
                      const int32_t *wt, uint32_t *lut, void *workspace, const uint8_t *labels,
-                     int32_t want, const uint32_t *fallback, hipStream_t stream) {
+                     int32_t want, int32_t nlabels, const uint32_t *fallback,
+                     hipStream_t stream) {
   if (fmt != SB_GUIDE_U16X2)
-    return build_sep(guide, fmt, sw, sh, lut_bits, wt, lut, workspace, labels, want, fallback,
-                     stream);
+    return build_sep(guide, fmt, sw, sh, lut_bits, wt, lut, workspace, labels, want, nlabels,
+                     fallback, stream);
   const LutGeom g = lut_geom(fmt, sw, sh, lut_bits);
   const LutWs w = lut_ws(workspace, g);
   const uint32_t nb = 1u << (2 * g.bucket_bits);
@@ -623,7 +653,8 @@ hipError_t build_one(const void *guide, int32_t fmt, int32_t sw, int32_t sh, int
 hipError_t launch_lut_build(const void *guide, int32_t fmt, int32_t sw, int32_t sh,
                             int32_t lut_bits, const int32_t wt[3], uint32_t *lut,
                             void *workspace, hipStream_t stream) {
-  return build_one(guide, fmt, sw, sh, lut_bits, wt, lut, workspace, nullptr, 0, nullptr, stream);
+  return build_one(guide, fmt, sw, sh, lut_bits, wt, lut, workspace, nullptr, 0, 0, nullptr,
+                   stream);
 }
 
 hipError_t launch_lut_build_labels(const void *guide, const uint8_t *labels, int32_t fmt,
@@ -633,7 +664,7 @@ hipError_t launch_lut_build_labels(const void *guide, const uint8_t *labels, int
   const size_t bins = size_t(1) << (fmt_channels(fmt) * lut_bits);
   for (int32_t l = 0; l < nlabels; ++l) {
     const hipError_t e = build_one(guide, fmt, sw, sh, lut_bits, wt, luts + size_t(l) * bins,
-                                   workspace, labels, l, lut, stream);
+                                   workspace, labels, l, nlabels, lut, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
