@@ -565,7 +565,7 @@ def anim_leg(sb, torch, np, workloads, style, w, h, p, nframes=12, reps=5):
     code changes between consecutive frames as a function of the threshold
     t -- static target with seeds re-drawn every frame (the flicker alone),
     moving target with seeds held (the motion alone) and moving target with
-    seeds re-drawn; 12-frame sequences as one graph launch; then sessions of
+    seeds re-drawn; 12-frame sequences as one batch; then sessions of
     60 fps frames served with in-order completion."""
     import paper_1807_03249_amd.serve as sv
 
@@ -648,7 +648,7 @@ def anim_leg(sb, torch, np, workloads, style, w, h, p, nframes=12, reps=5):
 
 def batch_leg(sb, at, torch, workloads, no_tune, reps=5):
     """64 frames of uneven size, half normal- and half UV-guided, 4 resident
-    styles: one autotuned graph launch per batch vs the same 64 frames through
+    styles: one autotuned batch plan run per batch vs the same 64 frames through
     the per-frame kernels, launched from one C call (sb_stylize_frames) with
     the same kernel choice."""
     import numpy as np
@@ -721,7 +721,7 @@ def batch_leg(sb, at, torch, workloads, no_tune, reps=5):
     out["mpixel"] = round(px / 1e6, 3)
     out["speedup"] = round(out["plain"]["ms_per_batch"] / out["graph"]["ms_per_batch"], 3)
     out["tune"] = list(pick["tune"]) if pick["tune"] else "default"
-    out["blocks_per_cu"] = pick["blocks_per_cu"] or 8
+    out["blocks_per_cu"] = pick["blocks_per_cu"] or "default"
     out["plain_launch"] = ("sb_stylize_frames (one C call, per-frame kernels, same tune); "
                            "plain_2_streams: the two halves of the list on two streams")
     return out
@@ -755,11 +755,13 @@ def serve_leg(sb, torch, np, workloads, nreq, qps):
     res = {"qps": qps, "requests": nreq, "budget_mib": 1024}
     # continuous batching: 8 slots (streams), each taking up to 4 admitted
     # requests per launch as direct launches with exact grids; the same on 4
-    # slots as captured graphs of up to 16; per-request launches on 8 slots
+    # slots as captured graphs of up to 16 (the grid given, so that every
+    # batch replays one); per-request launches on 8 slots
     # (no batching, same overlap); one stream, one request per launch, in
     # arrival order (the plain path)
     for name, kw in (("batched", dict(slots=8, max_batch=4, use_graph=False)),
-                     ("batched_graph_4", dict(slots=4, max_batch=16, use_graph=True)),
+                     ("batched_graph_4", dict(slots=4, max_batch=16, use_graph=True,
+                                             blocks_per_cu=16)),
                      ("per_request_8", dict(slots=8, max_batch=1)),
                      ("plain", dict(plain=True))):
         out = sv.run(reqs, budget_bytes=1 << 30, **kw)

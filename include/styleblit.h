@@ -521,7 +521,8 @@ size_t sb_frame_bytes(int32_t w, int32_t h);
 typedef struct {
     int32_t slots;      /* batches in flight, each on its own stream, 1..8 */
     int32_t max_batch;  /* frames per batch, 1..sb_batch_max_frames() */
-    int32_t use_graph;  /* batches as graph replays (1) or direct launches (0) */
+    int32_t use_graph;  /* batch plans with graphs (1) or direct launches only (0), as in
+                           sb_batch_create */
     int32_t plain;      /* 1: no batching; every request is its own sb_stylize on one
                            stream, in arrival order (the per-request baseline) */
     void *arena;        /* [device] outputs of requests in flight are carved from here:

@@ -9,8 +9,9 @@
 //   3. retires finished batches (event query), freeing their arena bytes and
 //      their slot;
 //   4. gives every free slot (its own stream, batch plan and workspace) all
-//      admitted requests up to max_batch, launched as one graph replay (a
-//      single request takes the per-frame kernels on the slot's stream).
+//      admitted requests up to max_batch, in one run of its batch plan (a
+//      graph replay or direct launches; a single request takes the per-frame
+//      kernels on the slot's stream).
 //      When a request belongs to a session (the frames of one animation)
 //      whose previous frame still runs on another slot, the slot's stream
 //      first waits for that slot's batch, so a session's frames complete in
