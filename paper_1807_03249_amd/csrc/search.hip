@@ -654,7 +654,7 @@ __global__ void __launch_bounds__(kMergeThreads) k_tree_merge(MergeArgs a) {
 // The unmarked texels one after another (in raster order within a workgroup's:
 // texels that a split cannot tell apart stay beside their neighbours), with their
 // coordinates and (with `box`) the box of them all.
-constexpr uint32_t kTakePer = 4;
+constexpr uint32_t kTakePer = 8;
 template <int D, int S>
 __global__ void __launch_bounds__(256) k_tree_take(MergeArgs a, void *vals, uint32_t *keys,
                                                    uint32_t *count, uint32_t *box) {
@@ -957,7 +957,7 @@ struct Sorter {
 // range take 38 us without the second element and 29 with it, its 1080p frame 696
 // and 587.)  Then the texels' entries and those of the three levels above them
 // are written.  Bound by the chain of exchanges (276 of them, 128 blocks for a
-// 512 x 512 style): 30 us; 70 with every exchange through LDS.
+// 512 x 512 style): 35 us; 75 with every exchange through LDS.
 template <int D, int S>
 __global__ void __launch_bounds__(512) k_tree_sort(SortArgs a) {
   __shared__ Tx<S> tex[kSortBlock];
