@@ -359,7 +359,7 @@ size_t sb_noalloc_scratch_bytes(void);
  *                4 (default 4, frames of up to 2^17 pixels 2); each vote
  *                gather loads that many texels
  *   blend_rows   rows of the voting tile: 8 or 16 (default 16, frames of up to
- *                2^17 pixels 8);
+ *                2^17 pixels and of 257 to 320 tiles of 64 x 16 pixels 8);
  *                the tile is (16 * blend_ppt) x blend_rows pixels, one thread
  *                per blend_ppt pixels
  *   level_group  levels of Algorithm 2 whose source-guide gathers are in
@@ -373,7 +373,7 @@ size_t sb_noalloc_scratch_bytes(void);
  *                and votes the other groups from a per-tile list; 1: every
  *                group votes in place (default 1; 2 for frames above
  *                2^21 pixels with a threshold that makes large chunks, and
- *                above 2^18 from radius 6 on; in batches 1) */
+ *                above 2^18 from radius 6 on, with 16 rows; in batches 1) */
 typedef struct {
     int32_t blend_ppt;
     int32_t blend_rows;

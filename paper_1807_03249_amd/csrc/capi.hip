@@ -164,6 +164,10 @@ bool resolve_weights(int32_t fmt, const uint8_t *in, int32_t out[3]) {
 // against 78, on noise likewise) the vote is bound by that.  Where they come from
 // one place 8 rows fit the chip more evenly (a 1080p normal-guided frame alone
 // 44.6 us against 45.8, but 37.2 against 36.0 with a second frame beside it).
+// Where 64 x 16 tiles leave the chip's 256 compute units a second round of up to
+// 64, it is worth it whatever the guide (640 x 480, 300 tiles: 0.84 to 0.93 of the
+// time of 16 rows and two blocks per wave, 16 rows and one 0.90 to 0.98; 720 x 576,
+// 432 tiles: up to 1.16 and 0.98).
 //
 // Copying uniform windows pays for its flags where most windows are uniform:
 // chunks are large when the threshold admits a step of two texels of a 16-bit
@@ -183,6 +187,8 @@ Tune frame_tune(const FrameArgs &a) {
                         : a.fmt == SB_GUIDE_U8X2 ? a.threshold >= 1024
                         : a.fmt == SB_GUIDE_U8X3 ? a.threshold >= 4096
                                                  : false;
+  const int32_t tiles = ((a.w + 63) / 64) * ((a.h + 15) / 16);
+  if (tiles > 256 && tiles <= 320) return Tune{4, 8, 2, 1, 1};
   const bool split = (tolerant && px > 1 << 21) || (a.radius >= 6 && px > 1 << 18);
   return Tune{4, 16, 2, px <= 1 << 19 ? 1 : 2, split ? 2 : 1};
 }

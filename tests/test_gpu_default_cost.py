@@ -42,10 +42,11 @@ def _style(sb, fmt, size, bits):
     return sb.Style(rgb, _as(fmt, g), bits)
 
 
-# 2^17 and 2^18 pixels about the radius from which uniform windows are copied, and
+# 256, 257, 320 and 330 tiles of 64 x 16, 2^17 and 2^18 pixels about the radius from which uniform windows are copied, and
 # 2^21 pixels about the thresholds that do
 @pytest.mark.parametrize("fmt,w,h,threshold,radius", [
-    ("u8x2", 512, 256, 32, 3), ("u16x2", 513, 256, 4096, 7), ("u8x3", 512, 512, 192, 6),
+    ("u8x2", 1024, 256, 32, 3), ("u16x2", 1025, 256, 4096, 5), ("u8x3", 640, 512, 192, 7),
+    ("u8x2", 704, 480, 32, 7), ("u8x2", 8192, 33, 32, 2), ("u8x2", 512, 256, 32, 3), ("u16x2", 513, 256, 4096, 7), ("u8x3", 512, 512, 192, 6),
     ("u8x2", 513, 512, 32, 5), ("u8x2", 513, 512, 32, 6), ("u16x2", 1025, 512, 4096, 7),
     ("u8x2", 2048, 1024, 1024, 2), ("u8x2", 2049, 1024, 1024, 2), ("u8x2", 2049, 1024, 1023, 2),
     ("u16x2", 2049, 1024, 1 << 20, 1), ("u16x2", 2049, 1024, (1 << 20) - 1, 1),
@@ -66,9 +67,11 @@ def test_lines_of_the_default(sb, fmt, w, h, threshold, radius):
 
 
 # texture coordinates that jump over the exemplar (8 rows a tile took 1.28 times 16
-# rows there), and noise, at few pixels (2 pixels a thread took 1.4 times 4)
+# rows there), and noise, at few pixels (2 pixels a thread took 1.4 times 4); tiles that leave a second
+# round of a few (16 rows took 1.09 times 8)
 @pytest.mark.parametrize("w,h,noise,radius,tune", [(1920, 1080, False, 3, (4, 16, 2, 2, 1)),
-                                                   (600, 400, True, 7, (4, 16, 2, 1, 1))])
+                                                   (600, 400, True, 7, (4, 16, 2, 1, 1)),
+                                                   (640, 480, False, 3, (4, 8, 2, 1, 1))])
 def test_scattered_texels_cost(sb, w, h, noise, radius, tune):
     import torch
 
@@ -97,4 +100,4 @@ def test_scattered_texels_cost(sb, w, h, noise, radius, tune):
             t[1].record()
             t[1].synchronize()
             best[i] = min(best[i], t[0].elapsed_time(t[1]))
-    assert best[0] < 1.12 * best[1]
+    assert best[0] < 1.07 * best[1]
