@@ -146,3 +146,56 @@ def test_equal_values_of_an_axis(sb, depth, channels, steps):
     at_keys = 256 + _up256(_start(levels - 1) * 16 * t) + _up256((n + 7) // 8 * 8 * t)
     keys = st.tree.cpu().numpy()[at_keys:at_keys + (_start(levels) + n) * 4].view(np.uint32)
     np.testing.assert_array_equal(keys[_start(levels):], _leaves(values.astype(np.int64), depth))
+
+
+@pytest.mark.parametrize("depth,channels", [(16, 8), (16, 5), (8, 8)])
+def test_values_of_the_guide(sb, depth, channels):
+    """Lookups of every value of a guide of noise, those that a median put beside
+    equal ones among them: each its own texel."""
+    import torch
+
+    rng = np.random.default_rng(depth + channels)
+    size, top = 150, (1 << depth) - 1
+    elems = oracle.texel_bytes(depth, channels) * 8 // depth
+    g = rng.integers(0, top + 1, (size, size, elems)).astype(np.uint8 if depth == 8 else np.uint16)
+    print(f"[gpu-case] values of the guide {depth}x{channels}", flush=True)
+    st = sb.Style(np.zeros((size, size, 3), np.uint8), g, channels=channels)
+    order = rng.permutation(size * size)
+    q = np.ascontiguousarray(g.reshape(-1, elems)[order])
+    values, first, back = np.unique(q[:, :channels], axis=0, return_index=True, return_inverse=True)
+    least = np.full(len(values), size * size)
+    np.minimum.at(least, back.ravel(), order)
+    want = least[back.ravel()]
+    want = (want // size << 16 | want % size).astype(np.uint32)
+    t = torch.from_numpy(q.view(np.int16) if depth == 16 else q).cuda()
+    np.testing.assert_array_equal(st.query(t).cpu().numpy().view(np.uint32), want)
+    t = torch.cat([t] * 4)  # more than 65536: four lanes a lookup
+    np.testing.assert_array_equal(st.query(t).cpu().numpy().view(np.uint32), np.tile(want, 4))
+
+
+def test_cost_of_exact_lookups(sb):
+    """The values of a guide of eight channels of noise cost little more than those
+    of a guide of four (7 times when searches bounded by a far texel went on)."""
+    import torch
+
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+
+    def ms(channels):
+        v = torch.randint(0, 65536, (200, 200, channels), generator=gen, device="cuda")
+        g = v.to(torch.int16).contiguous()
+        st = sb.Style(torch.zeros(200, 200, 3, dtype=torch.uint8, device="cuda"), g, channels=channels)
+        q = torch.cat([g.reshape(-1, channels)] * 3)
+        best = float("inf")
+        for _ in range(7):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            for _ in range(5):
+                st.query(q)
+            t[1].record()
+            t[1].synchronize()
+            best = min(best, t[0].elapsed_time(t[1]))
+        return best
+
+    print("[gpu-case] cost of exact lookups", flush=True)
+    assert ms(8) < 4 * ms(4)
