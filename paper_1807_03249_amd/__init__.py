@@ -189,7 +189,7 @@ def _stream(torch) -> int:
     """Handle of torch's current stream on the current device.  Small frames
     wait for the host, so without a Stream object: 0.2 us instead of 2.8 for
     torch.cuda.current_stream().cuda_stream (an animation step of 853 x 481,
-    three calls, took 41 us with it and 35 without)."""
+    three calls, took 41 us with it and 36 without)."""
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 

@@ -35,8 +35,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Default workgroups per compute unit of the persistent grids: twice what a
 // unit holds, so that one with cheap tiles takes more of them (64 frames
-// 1060 us, with 12 1079 and with 8 1137, before their kernels were scheduled for
-// their waves: 1019).
+// 1060 us, with 12 1079 and with 8 1137, before the level loop's waves hint: 1019).
 constexpr uint32_t kBlocksPerCu = 16;
 // Pixels per workgroup of that grid from which a graph is replayed.
 constexpr uint64_t kGraphPixels = 6144;

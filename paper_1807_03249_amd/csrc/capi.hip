@@ -120,7 +120,8 @@ bool fill_frame(const sb_style *style, const void *tgt_guide, int32_t w, int32_t
   // (8-bit two-channel styles, 256 KiB), and else on frames that the pass would
   // hold up more than the lookups (320 x 240 appearance 14.1 us, with the pass
   // 18.8; 640 x 480 texture coordinates 16.5 and 19.9; 1080p 44.6 and 46.2, with
-  // labels 54.1 and 56.4; 4K 140 and 135, with labels 165 and 161)
+  // labels 54.1 and 56.4; 2048 x 1536 63.4 and 63.6, with labels 81.8 and 83.6;
+  // 2560 x 1600 76.3 and 75.2; 4K 140 and 135, with labels 165 and 161)
   const Levels &lv = a->lv;
   a->own_seeds = (lv.count == 0 || lv.log2_spacing[lv.count - 1] >= 3) &&
                  ((style->fmt == SB_GUIDE_U8X2 && tgt_labels == nullptr) ||
@@ -194,7 +195,8 @@ Tune frame_tune(const FrameArgs &a) {
 }
 
 // A batch fills the chip: large tiles for the least halo (64 frames of 0.3 to
-// 2 Mpixel 1060 us, with 8 rows 1091, with uniform windows copied 1101).
+// 2 Mpixel 1060 us, with 8 rows 1091, with uniform windows copied 1101, before the
+// level loop's hint: 1019).
 Tune batch_tune() { return Tune{4, 16, 2, 2, 1}; }
 
 bool resolve_tune(const sb_tune *in, const Tune &base, Tune *out) {

@@ -509,7 +509,7 @@ __device__ __forceinline__ void lut_query(const uint32_t *start, const uint2 *pt
 // The table, a thread per bin or, where that pays, per 2 x 2 bins of one bucket
 // (buckets are at least two bins wide from two bits per channel on).  It pays on
 // evenly filled buckets (4 M bins of a 2048 x 2048 guide of texture coordinates
-// 15.6 us, 26 with one bin a thread): where the pixels crowd in a few, the walks
+// 15.2 us, 19 with one bin a thread): where the pixels crowd in a few, the walks
 // are long and a quarter of the threads waits too much for each (a 512 x 512
 // guide of constant regions at 9 bits 211 ms, 818 with 2 x 2 bins).
 // `fallback` (may be null): when no pixel was bucketed (a label absent from

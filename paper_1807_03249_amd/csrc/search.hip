@@ -647,14 +647,15 @@ __device__ __forceinline__ bool same_texel(const Tx<S> &a, const Tx<S> &b, const
 
 // Texels equal in every channel are one to a search, and a tree that holds each
 // many times has whole levels of boxes at one distance, all of which a lookup has
-// to enter (a constant 512 x 512 guide: 65536 lookups 202 us, 11 with one texel).
+// to enter (a constant 512 x 512 guide: 65536 lookups 202 us, 6.4 with one texel).
 // So every texel but the first of its value is marked: whenever two equal ones
 // meet, the one of larger index.  The texels of a workgroup meet in LDS first (the
 // smallest index of each hash's place there, so a texel equal to that one is done):
 // a constant region sends one of a workgroup's 1024 to the slot that all of them
 // share, where atomics follow one another at 16 ns.  A probe that finds another
-// value's slot goes on by an odd step of the hash; a quarter of the slots or fewer
-// are ever taken, so a wave's longest chain is about three.
+// value's slot goes on by an odd step of the hash; a third of the slots or fewer are
+// ever taken, so chains are short.  Bound by them and by the round trips before: 17 us
+// for 512 x 512 texels (23 with two thirds taken).
 template <int S>
 __global__ void __launch_bounds__(kMergeThreads) k_tree_merge(MergeArgs a) {
   __shared__ uint32_t first[kMergeThreads];
@@ -1348,9 +1349,9 @@ __global__ void __launch_bounds__(256) k_assign_n(FrameArgs a) {
 // Without levels there is no table; every pixel falls back then, and the
 // waves take every n-th tile.
 //
-// Bound by VALU issue (69 % of the chip's over the pass, 215 instructions per
+// Bound by VALU issue (64 % of the chip's over the pass, 215 instructions per
 // node of a wave's 32 searches) and by the last searches.  The 414 k searches
-// of a 1080p frame with five 8-bit channels: 330 us; one search per lane in
+// of a 1080p frame with five 8-bit channels: 337 us; one search per lane in
 // the linked binary tree took 1300.  Fixed 16 x 16 tiles per workgroup 440,
 // draws of 8 x 8 370; four lanes per search instead of two 350 (for four
 // 16-bit channels 610 k searches in 245, and 320 with four lanes).
