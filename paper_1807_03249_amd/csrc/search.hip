@@ -652,13 +652,16 @@ __device__ __forceinline__ bool same_texel(const Tx<S> &a, const Tx<S> &b, const
 // meet, the one of larger index.  The texels of a workgroup meet in LDS first (the
 // smallest index of each hash's place there, so a texel equal to that one is done):
 // a constant region sends one of a workgroup's 1024 to the slot that all of them
-// share, where atomics follow one another at 16 ns.  A probe that finds another
+// share, where atomics follow one another at 16 ns.  A texel whose place went to
+// another value has a second one, from other bits: with one alone, two values that
+// share it and fill a guide send half of all texels to one slot (512 x 512 of two
+// such values register in 126 us, 1755 with one place).  A probe that finds another
 // value's slot goes on by an odd step of the hash; a third of the slots or fewer are
 // ever taken, so chains are short.  Bound by them and by the round trips before: 17 us
 // for 512 x 512 texels (23 with two thirds taken).
 template <int S>
 __global__ void __launch_bounds__(kMergeThreads) k_tree_merge(MergeArgs a) {
-  __shared__ uint32_t first[kMergeThreads];
+  __shared__ uint32_t first[2][kMergeThreads];
   const uint32_t tid = threadIdx.x, i = blockIdx.x * kMergeThreads + tid;
   const Tx<S> t = load_tx<S>(a.guide, min(i, a.n - 1u));
   uint32_t h = 0;
@@ -669,17 +672,21 @@ __global__ void __launch_bounds__(kMergeThreads) k_tree_merge(MergeArgs a) {
   }
   h *= 0x9E3779B1u;
   h ^= h >> 16;
-  first[tid] = kNoTexel;
+  first[0][tid] = first[1][tid] = kNoTexel;
   __syncthreads();
-  uint32_t *place = &first[(h >> 16) % kMergeThreads];
-  if (i < a.n) atomicMin(place, i);
-  __syncthreads();
-  if (i >= a.n) return;
-  const uint32_t f = *place;
-  if (f != i && same_texel<S>(load_tx<S>(a.guide, f), t, a.mask)) {
-    a.dup[i] = 1;
-    return;
+  const bool in = i < a.n;
+  bool dup = false, done = !in;
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    uint32_t *place = &first[r][(r ? h >> 4 : h >> 16) % kMergeThreads];
+    if (!done) atomicMin(place, i);
+    __syncthreads();
+    const uint32_t f = *place;
+    if (!done && f != i) dup = same_texel<S>(load_tx<S>(a.guide, f), t, a.mask);
+    done |= dup | (f == i);
   }
+  if (dup) a.dup[i] = 1;
+  if (dup || !in) return;
   for (uint32_t s = h;; s += (h >> 12) | 1u) {
     uint32_t *slot = a.table + (s & (a.slots - 1u));
     uint32_t v = atomicCAS(slot, kNoTexel, i);

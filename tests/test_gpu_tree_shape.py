@@ -199,3 +199,44 @@ def test_cost_of_exact_lookups(sb):
 
     print("[gpu-case] cost of exact lookups", flush=True)
     assert ms(8) < 4 * ms(4)
+
+
+def _places(words):
+    """The first place that equal texels of two words meet at."""
+    h = np.zeros(len(words), np.uint32)
+    for w in words.T:
+        h = (h ^ w) * np.uint32(0x9E3779B1)
+        h ^= h >> np.uint32(15)
+    h *= np.uint32(0x9E3779B1)
+    h ^= h >> np.uint32(16)
+    return (h >> np.uint32(16)) % 1024
+
+
+def test_cost_of_values_of_one_place(sb):
+    """Two values that meet at one place register in the time of two that do not."""
+    import torch
+
+    values = np.random.default_rng(8).integers(0, 65536, (200, 4)).astype(np.uint16)
+    place = _places(values.view(np.uint32))
+    same = np.argwhere((place[:, None] == place) & (np.arange(200)[:, None] < np.arange(200)))
+    assert len(same) and place[0] != place[1]
+    pick = torch.randint(0, 2, (512, 512), generator=torch.Generator().manual_seed(8)).cuda()
+    rgb = torch.zeros(512, 512, 3, dtype=torch.uint8, device="cuda")
+
+    def ms(two):
+        g = torch.from_numpy(values[two].astype(np.int32)).cuda()[pick].to(torch.int16).contiguous()
+        best = float("inf")
+        for _ in range(7):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            st = sb.Style(rgb, g, channels=4)
+            t[1].record()
+            t[1].synchronize()
+            best = min(best, t[0].elapsed_time(t[1]))
+            del st
+        return best
+
+    print("[gpu-case] cost of values of one place", flush=True)
+    apart, together = ms([0, 1]), ms(list(same[0]))
+    print(f"{apart * 1e3:.0f} us, {together * 1e3:.0f} us of one place")
+    assert together < 2 * apart
